@@ -513,8 +513,13 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
     constexpr int VM_AFTER = (LEAD - 1 - P::PF) * (2 + 2 * V16);
     static_assert(VM_AFTER >= 0 && VM_AFTER < 64, "vmcnt range");
     static_assert(P::LAM_D >= LEAD - P::PF, "lambda requests precede the slices waited for");
+    constexpr int VM_DRAIN = (7 << 4) | (15 << 8);  // vmcnt(0) only
     constexpr int WAIT = (VM_AFTER & 15) | (7 << 4) | (0 << 8) | ((VM_AFTER >> 4) << 14);
-    __syncthreads();  // (waits for every request: the first LEAD steps' slices are in LDS)
+    // The first LEAD steps' slices and lambda entries must be in LDS for every
+    // wave.  A workgroup barrier does not wait for loads into LDS (it waits for
+    // the LDS counter only), so each wave waits for its own requests first.
+    __builtin_amdgcn_s_waitcnt(VM_DRAIN);
+    __syncthreads();
     if constexpr (P::PREF) opload(reinterpret_cast<const Tin*>(ring), saX);
     for (int J = 0; 2 * J < m; ++J) {
       if (J > 0) {
@@ -541,6 +546,9 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[NT - 1][r] += wP * f[NT - 1][r];
     }
+    // requests of the steps past the last one may still be on their way into
+    // the ring, whose bytes the keys take next
+    __builtin_amdgcn_s_waitcnt(VM_DRAIN);
   }
   __syncthreads();  // the state ring and the lambda blocks are no longer read
 
