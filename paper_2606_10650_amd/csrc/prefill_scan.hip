@@ -33,7 +33,7 @@
 #include <type_traits>
 
 #include "mfma.h"
-#include "prefill.h"
+#include "scan_decide.h"
 
 namespace dla {
 
@@ -97,10 +97,6 @@ hipError_t launch_prefill_prep(const PrefillArgs& a, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // stage 2
 // ---------------------------------------------------------------------------
-constexpr int SL = 64;  // tokens per scan chunk (one per lane of a wavefront)
-constexpr int SWAVE = 8;  // waves per scan workgroup
-constexpr int STHR = 64 * SWAVE;
-
 typedef u32x4 u32x4s;
 
 template <int DK, int DV, typename Tin>
@@ -119,24 +115,31 @@ struct ScanP {
   static constexpr bool TRANS = E == 2;
   static constexpr int NTERM = E == 2 ? 3 : 1;  // bf16 terms that carry a float32 value
   // sK, sV, sP and sVV are contiguous and dead once the tables are built; for
-  // 16-bit inputs the decayed keys of the state advance (NTERM x [DK][TRS])
-  // reuse their bytes (float32 inputs form them in the advance instead)
-  static constexpr size_t DEAD_BYTES = (size_t)SL * (KRS + VRS) * E + 2 * (size_t)SL * (SL + 1) * 4;
-  static_assert((size_t)NTERM * DK * TRS * E <= DEAD_BYTES, "decayed keys");
+  // 16-bit inputs the decayed keys of the state advance (NTERM x [DK][TRS]) and
+  // the decisions' row tables reuse their bytes; float32 inputs form the
+  // decayed keys in the advance instead, from sK and sV, and the row tables
+  // take those of sP and sVV
+  static constexpr size_t KV_BYTES = (size_t)SL * (KRS + VRS) * E;
+  static constexpr size_t KD_BYTES = TRANS ? (size_t)NTERM * DK * TRS * E : 0;
+  static constexpr size_t ROW_OFF = TRANS ? KD_BYTES : KV_BYTES;
+  static constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
+  static constexpr size_t DEAD_BYTES =
+      cmax(KV_BYTES + 2 * (size_t)SL * (SL + 1) * 4, ROW_OFF + RowTables::BYTES);
+  static_assert(ROW_OFF % 16 == 0 && DEAD_BYTES % 16 == 0, "alignment");
   static size_t smem_bytes(int C) {
     size_t off = DEAD_BYTES;                            // sK, sV, sP, sVV
     off += TRANS ? (size_t)(DK + DV) * TRS * E : 0;     // sKt, sVt
     off += (size_t)SL * (SL + 1) * 4;                   // sR
     off += (size_t)SWAVE * SL * 4;                      // sPart
-    off += (size_t)SL * 4 * 8;                          // float rows
-    off += (size_t)SL * 4 * 3 + SL * 2;                 // int rows, int8 rows
-    off = round_up(off, 8);
-    off += (size_t)C * (8 + 4 + 4) + 64;
+    off += (size_t)SL * 4 * 8;                          // float rows, int rows
+    off += 64;                                          // sMisc
+    if (C > kMaxRegC) off += (size_t)C * (8 + 4 + 4);
     return round_up(off, 16);
   }
 };
 
-template <int DK, int DV, typename Tin>
+// NR: the states' bookkeeping in NR registers per lane and field, or in LDS (0).
+template <int DK, int DV, typename Tin, int NR>
 __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, PrefillWS w, int tb,
                                                             int te) {
   if (!cache_matches(a.cache, a.desc)) return;  // refused call (see the prep kernel)
@@ -180,18 +183,10 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
   float* sDe = sAl2 + SL;      // exp(G_end - G_t)
   float* sa = sDe + SL;        // |k_t|^2 |v_t|^2
   float* sc0 = sa + SL;        // k_t^T S_0 v_t
-  float* sIo = sc0 + SL;       // scores
-  float* sRed = sIo + SL;      // reductions (8 floats used)
-  int32_t* sMo = reinterpret_cast<int32_t*>(sRed + SL);  // merge overrides
-  int32_t* sMout = sMo + SL;                             // merge indices
-  int32_t* sDC = sMout + SL;                             // death tokens of the chunk's tokens
-  int8_t* sBo = reinterpret_cast<int8_t*>(sDC + SL);     // boundary overrides
-  int8_t* sBout = sBo + SL;                              // boundaries
-  char* q8 = reinterpret_cast<char*>(sBout + SL);
-  double* sIb = reinterpret_cast<double*>(smem + round_up((size_t)(q8 - smem), 8));  // [C]
-  int32_t* sN = reinterpret_cast<int32_t*>(sIb + C);  // [C]
-  int32_t* sLead = sN + C;                            // [C]
-  int32_t* sMisc = sLead + C;                         // m, p_last
+  float* sRed = sc0 + SL;      // reductions (8 floats used)
+  int32_t* sBo = reinterpret_cast<int32_t*>(sRed + SL);  // boundary overrides
+  int32_t* sMisc = sBo + SL;   // last boundary of the chunk, start of the row tables
+  const RowTables rows(smem + P::ROW_OFF);
   __shared__ double sGlast[1];
 
   Meta M = meta_at(a.cache + a.meta_offset + (size_t)h * a.meta_stride, C);
@@ -199,21 +194,23 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
   ScarryView sv = scarry_at(w, h, C);
   // states present before the call (copied from the cache by stage 1)
   const int m0 = *iv.m0;
-  if (tb == 0) {
-    for (int j = tid; j < C; j += STHR) {
-      sIb[j] = M.ibar[j];
-      sN[j] = M.n[j];
-      sLead[j] = j - m0;
-    }
-    if (tid == 0) sMisc[0] = m0;
-  } else {
-    // resume where the previous segment stopped
-    for (int j = tid; j < C; j += STHR) {
-      sIb[j] = sv.ibar[j];
-      sN[j] = sv.n[j];
-      sLead[j] = sv.lead[j];
-    }
-    if (tid == 0) sMisc[0] = *sv.m;
+  // the states' bookkeeping, wave 0's: resumed where the previous segment stopped
+  using States = typename std::conditional<NR == 0, StatesInLds, StatesInRegs<NR>>::type;
+  ChunkDecider<States> dec;
+  dec.st.C = C;
+  if constexpr (NR == 0) {
+    dec.st.I = reinterpret_cast<double*>(sMisc + 16);  // [C]
+    dec.st.n = reinterpret_cast<int32_t*>(dec.st.I + C);
+    dec.st.ld = dec.st.n + C;
+  }
+  dec.m = 0;
+  dec.B = 0;
+  if (wv == 0) {
+    if (tb == 0)
+      dec.st.load(M.ibar, M.n, nullptr, m0);
+    else
+      dec.st.load(sv.ibar, sv.n, sv.lead, m0);
+    dec.m = __builtin_amdgcn_readfirstlane(tb == 0 ? m0 : *sv.m);
   }
 
   // newest state at the start of the call, true (decayed) values, as MFMA
@@ -360,16 +357,12 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
       // alpha_t^2 = exp(2 g_t); only tokens of the chunk read their predecessor
       sAl2[t] = (t < nrow) ? __expf(2.f * (t == 0 ? gc : gc - gcp)) : 0.f;
       sDe[t] = (t < nrow) ? __expf((float)(Glast - Gt)) : 0.f;
-      sBo[t] = (int8_t)bpre;
-      sMo[t] = mpre;
-      sDC[t] = -1;
-      sBout[t] = 0;
-      sMout[t] = -1;
-      sIo[t] = 0.f;
+      sBo[t] = bpre;
       if (t == 0) sGlast[0] = Glast;
     }
     __syncthreads();
     const double Gnext = sGlast[0];  // G after the chunk's last token
+    const int mforce = mpre;  // merge override of the lane's token (wave 0)
     if (c0 + SL < te) prefetch(c0 + SL);
 
     // ------------------------------------------------ Gram products and the carry term
@@ -514,148 +507,79 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
         }
       }
     }
+    RowIn rin;
+    rin.nrow = nrow;
+    rin.C = C;
+    rin.D = Df;
+    rin.tau = tau;
+    rin.eps = a.eps;
+    rin.eps_rms = a.eps_rms;
+    rin.a = sa[lane];
+    rin.al2n = (lane + 1 < SL) ? sAl2[lane + 1] : 0.f;
+    rin.bo = sBo[lane];
+    // c and growth 2 c + a of |S|^2 for a state that began at p >= 0 of the chunk
+    auto row = [&](int p, float& ct, float& inc) __attribute__((always_inline)) {
+      ct = (lane > p) ? sR[lane * (SL + 1) + p] : 0.f;
+      inc = 2.f * ct + rin.a;
+    };
+    auto open_at = [&](int ts, float Is) __attribute__((always_inline)) {
+      dec.open(ts, Is, mforce, c0, C, T, &reinterpret_cast<CacheHeader*>(a.cache)->flags,
+               [&](int ld, int tk) { (ld >= 0 ? death[ld] : iv.death0[ld + m0]) = tk; });
+    };
     if (wv == 0) {
-      const int t = lane;
-      const float at = sa[t];
-      const float c0t = sc0[t];
-      const float At = sA[t];
-      const float al2n = (t + 1 < SL) ? sAl2[t + 1] : 0.f;  // alpha^2 of token t+1
-      int mcur = sMisc[0];
-      int p = -1;  // start of the newest state: -1 = before the chunk
-      int plast = -1;
-      if (mcur == 0) {
+      const int nseq = __popcll(dec.B) >= NSEQ ? 1 : NSEQ;
+      dec.p = -1;
+      dec.B = 0;
+      dec.mo = -1;
+      dec.dc = -1;
+      dec.io = 0.f;
+      if (dec.m == 0) {
         // the first token of an empty cache opens a state with score 0
-        if (lane == 0) {
-          sBout[0] = 1;
-          sIo[0] = 0.f;
-          sMout[0] = -1;
-          sN[0] = 1;
-          sIb[0] = 0.0;
-          sLead[0] = c0;
-          sDC[0] = T;
-        }
-        mcur = 1;
-        p = 0;
-        plast = 0;
+        dec.st.push(0, 0.0, c0);
+        dec.m = 1;
+        dec.p = 0;
+        dec.B = 1;
+        if (lane == 0) dec.dc = T;
       }
-      while (true) {
-        const int first = p + 1;  // first token scored against this state
-        float ct;
-        if (p < 0)
-          ct = At * c0t + sR[t * (SL + 1)];  // R[0][t]
-        else
-          ct = (t > p) ? sR[t * (SL + 1) + p] : 0.f;
-        // |S|^2 before token t: b(t+1) = alpha_{t+1}^2 (b(t) + 2 c(t) + a_t), b(first) = binit
-        const float binit = (p < 0) ? sA[0] * sA[0] * b0 : 0.f;
-        const int ustart = (p < 0) ? 0 : p;
-        float Am = 1.f, Bm = 0.f;
-        if (t >= ustart) {
-          Am = al2n;
-          Bm = al2n * (2.f * ct + at);
-        }
-        // inclusive scan of the affine maps x -> Am x + Bm over lanes
-        wave_scan_affine(Am, Bm);
-        const float bnext = Am * binit + Bm;  // b(t+1)
-        float bt = dpp_f<0x138, 0xF>(binit, bnext);  // lane t - 1
-        if (t == ustart) bt = binit;
-        if (p < 0 && t == 0) bt = binit;
-        const bool valid = (t < nrow) && (t >= first);
-        const float It = valid ? score_f(at, bt, ct, Df, a.eps, a.eps_rms) : 0.f;
-        int bd = (It >= tau) ? 1 : 0;
-        if (sBo[t] != -1) bd = sBo[t] ? 1 : 0;
-        if (C == 1) bd = 0;
-        const uint64_t mask = __ballot(valid && bd);
-        const int tstar = mask ? (__ffsll((unsigned long long)mask) - 1) : nrow;
-        // tokens first .. tstar-1 join the newest state
-        const bool joins = valid && t < tstar;
-        if (joins) sIo[t] = It;
-        const double sI = wave_sum_d(joins ? (double)It : 0.0);
-        if (lane == 0 && tstar > first) {
-          sN[mcur - 1] += tstar - first;
-          sIb[mcur - 1] += sI;
-        }
-        if (tstar >= nrow) break;
-        // boundary at tstar: Alg. 2 when the cache is full, then a new state
-        const float Istar = __shfl(It, tstar, 64);
-        int istar = -1;
-        if (mcur == C) {
-          double best = INFINITY;
-          int bi = 0x7fffffff;
-          for (int i = lane; i + 1 < C; i += 64) {
-            const double d = (sIb[i] + sIb[i + 1]) / (double)(sN[i] + sN[i + 1]);
-            if (d < best) {
-              best = d;
-              bi = i;
+      const float c0t = sc0[lane], At = sA[lane];
+      const bool more = dec.first_rows(
+          rin, nseq,
+          [&](int p, float& ct, float& inc, float& binit) __attribute__((always_inline)) {
+            binit = 0.f;
+            if (p < 0) {
+              ct = At * c0t + sR[lane * (SL + 1)];  // R[0][t]
+              inc = 2.f * ct + rin.a;
+              binit = sA[0] * sA[0] * b0;
+            } else {
+              row(p, ct, inc);
             }
-          }
-          wave_argmin_d(best, bi);
-          // NaN densities (scores from non-finite inputs) compare false, so a
-          // sequential argmin that starts at pair 0 never moves to them, and
-          // stays at pair 0 when pair 0's density is NaN or none is a number
-          istar = (bi >= 0 && bi <= C - 2) ? bi : 0;
-          if (__builtin_isnan((sIb[0] + sIb[1]) / (double)(sN[0] + sN[1]))) istar = 0;
-          const int fo = sMo[tstar];
-          if (fo != -1) {
-            if (fo >= 0 && fo <= C - 2)
-              istar = fo;
-            else if (lane == 0)
-              atomicOr(&reinterpret_cast<CacheHeader*>(a.cache)->flags, DLA_FLAG_BAD_MERGE_OVERRIDE);
-          }
-          // the state right of the pair dies at token c0 + tstar
-          const int ld = sLead[istar + 1];
-          if (lane == 0) {
-            if (ld >= c0)
-              sDC[ld - c0] = c0 + tstar;
-            else if (ld >= 0)
-              death[ld] = c0 + tstar;
-            else
-              iv.death0[ld + m0] = c0 + tstar;
-          }
-          // merge istar, istar+1 and shift the later states down, 64 entries at a
-          // time in increasing order (a block's writes never touch entries that a
-          // later block still has to read)
-          for (int j0 = istar; j0 + 1 < mcur; j0 += 64) {
-            const int j = j0 + lane;
-            const bool act = j + 1 < mcur;
-            double nI = 0.0;
-            int nN = 0, nL = 0;
-            if (act) {
-              nI = (j == istar) ? sIb[j] + sIb[j + 1] : sIb[j + 1];
-              nN = (j == istar) ? sN[j] + sN[j + 1] : sN[j + 1];
-              nL = (j == istar) ? sLead[j] : sLead[j + 1];
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (act) {
-              sIb[j] = nI;
-              sN[j] = nN;
-              sLead[j] = nL;
-            }
-            __builtin_amdgcn_wave_barrier();
-          }
-          mcur -= 1;
-        }
-        if (lane == 0) {
-          sBout[tstar] = 1;
-          sIo[tstar] = Istar;
-          sMout[tstar] = istar;
-          sN[mcur] = 1;
-          sIb[mcur] = (double)Istar;
-          sLead[mcur] = c0 + tstar;
-          sDC[tstar] = T;
-        }
-        mcur += 1;
-        p = tstar;
-        plast = tstar;
-      }
+          },
+          open_at);
       if (lane == 0) {
-        sMisc[0] = mcur;
-        sMisc[1] = plast;
+        sMisc[0] = dec.B ? 63 - __clzll((long long)dec.B) : -1;
+        sMisc[1] = more ? dec.p : -1;
       }
     }
     __syncthreads();
+    const int prow = sMisc[1];
+    if (prow >= 0) {  // (workgroup-uniform)
+      fill_rows(rin, prow, rows, row);
+      __syncthreads();
+      if (wv == 0) {
+        dec.finish_rows(rin, rows, open_at);
+        if (lane == 0) sMisc[0] = 63 - __clzll((long long)dec.B);
+      }
+      __syncthreads();
+    }
+    if (wv == 0 && lane < nrow) {
+      death[c0 + lane] = dec.dc;
+      if (a.b_out) a.b_out[tok0 + c0 + lane] = (int8_t)((dec.B >> lane) & 1);
+      if (a.merge_out) a.merge_out[tok0 + c0 + lane] = dec.mo;
+      if (a.score_out) a.score_out[tok0 + c0 + lane] = dec.io;
+    }
 
     // ------------------------------------------------ advance the newest state
-    const int plast = sMisc[1];
+    const int plast = sMisc[0];
     {
       const float sc = (plast < 0) ? sA[nrow - 1] : 0.f;
 #pragma unroll
@@ -708,29 +632,15 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
       }
     }
     b0 = state_norm2();  // (contains a barrier)
-    if (tid < nrow) {
-      const int t = tid;
-      death[c0 + t] = sDC[t];
-      if (a.b_out) a.b_out[tok0 + c0 + t] = sBout[t];
-      if (a.merge_out) a.merge_out[tok0 + c0 + t] = sMout[t];
-      if (a.score_out) a.score_out[tok0 + c0 + t] = sIo[t];
-    }
     Gprev = Gnext;
   }
-  __syncthreads();
-  const int mfin = sMisc[0];
   if (te == T) {
-    for (int j = tid; j < mfin; j += STHR) {
-      M.n[j] = sN[j];
-      M.ibar[j] = sIb[j];
-    }
+    if (wv == 0) dec.st.store(M.ibar, M.n, nullptr, dec.m);
   } else {
-    for (int j = tid; j < mfin; j += STHR) {
-      sv.ibar[j] = sIb[j];
-      sv.n[j] = sN[j];
-      sv.lead[j] = sLead[j];
+    if (wv == 0) {
+      dec.st.store(sv.ibar, sv.n, sv.lead, dec.m);
+      if (lane == 0) *sv.m = dec.m;
     }
-    if (tid == 0) *sv.m = mfin;
 #pragma unroll
     for (int k = 0; k < NTW; ++k)
       if (tok(k)) {
@@ -754,27 +664,28 @@ bool prefill_scan_supported(const dla_cache_desc& d, dla_dtype in_dtype) {
   return d.d_v == 128 ? fits(I64{}, I128{}) : fits(I64{}, I64{});
 }
 
+template <int DK, int DV, typename Tin>
+static hipError_t launch_scan_t(const PrefillArgs& a, const PrefillWS& w, int nh, int tb, int te,
+                                hipStream_t s) {
+  const size_t shm = ScanP<DK, DV, Tin>::smem_bytes(a.desc.C);
+  if (shm > 160 * 1024) return hipErrorInvalidValue;
+  auto launch = [&](auto k) -> hipError_t {
+    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
+        hipSuccess)
+      return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3(nh), dim3(STHR), shm, s, a, w, tb, te);
+    return hipGetLastError();
+  };
+  if (a.desc.C > kMaxRegC) return launch(prefill_scan_kernel<DK, DV, Tin, 0>);
+  if (a.desc.C > 64) return launch(prefill_scan_kernel<DK, DV, Tin, 4>);
+  return launch(prefill_scan_kernel<DK, DV, Tin, 1>);
+}
+
 template <int DK, int DV>
 static hipError_t launch_scan_dims(const PrefillArgs& a, const PrefillWS& w, int nh, int tb,
                                    int te, hipStream_t s) {
-  if (a.in_dtype == DLA_F32) {
-    auto k = prefill_scan_kernel<DK, DV, float>;
-    const size_t shm = ScanP<DK, DV, float>::smem_bytes(a.desc.C);
-    if (shm > 160 * 1024) return hipErrorInvalidValue;
-    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
-        hipSuccess)
-      return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3(nh), dim3(STHR), shm, s, a, w, tb, te);
-  } else {
-    auto k = prefill_scan_kernel<DK, DV, bf16_t>;
-    const size_t shm = ScanP<DK, DV, bf16_t>::smem_bytes(a.desc.C);
-    if (shm > 160 * 1024) return hipErrorInvalidValue;
-    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
-        hipSuccess)
-      return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3(nh), dim3(STHR), shm, s, a, w, tb, te);
-  }
-  return hipGetLastError();
+  if (a.in_dtype == DLA_F32) return launch_scan_t<DK, DV, float>(a, w, nh, tb, te, s);
+  return launch_scan_t<DK, DV, bf16_t>(a, w, nh, tb, te, s);
 }
 
 hipError_t launch_prefill_scan(const PrefillArgs& a, int tb, int te, hipStream_t s) {
