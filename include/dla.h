@@ -337,9 +337,9 @@ dla_status dla_prefill_delta_workspace_size(const dla_cache_desc* desc, int32_t 
  * A token that joins the newest state adds k_t u_t^T to the decayed state,
  * with pseudo-value u_t = beta_t (v_t - (alpha_t S)^T k_t); a token that opens
  * one starts it at k_t (beta_t v_t)^T.  Every state is therefore the decayed
- * sum of k_s u_s^T over its tokens: a sequential scan (one workgroup per head,
- * the newest state on chip) makes the decisions and the pseudo-values, and the
- * chunked update and readout stages of dla_prefill run on (q, k, u, lambda)
+ * sum of k_s u_s^T over its tokens: a scan (one workgroup per head, the newest
+ * state on chip, 64 tokens at a time) makes the decisions and the pseudo-values,
+ * and the chunked update and readout stages of dla_prefill run on (q, k, u, lambda)
  * (u kept in float32 for the states; a bfloat16 copy for the readout of
  * 16-bit inputs).  The stages follow dla_prefill's schedule: pipelined (the
  * scan in segments on the library's second stream, joined back into `stream`

@@ -74,6 +74,60 @@ struct Frag<float> {
   }
 };
 
+// 16 x 16 output tiles, K = 32 per step: lane l holds row (A) or column (B)
+// l % 16 and 8 k-values, the k set being the lane quarter's; as above, any
+// assignment of (lane quarter, element) to k that A and B share gives the same
+// sum.  Output: lane l holds column l % 16 and rows 4 (l / 16) + r, r = 0..3.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void mma16(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma16(f32x4& acc, const f32x8& a, const f32x8& b) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
+}
+// the K = 16 product of float32 operands, 4 k-values per lane
+__device__ __forceinline__ void mma16(f32x4& acc, const f32x4& a, const f32x4& b) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
+}
+
+// A float32 operand as three bfloat16 terms, largest first, whose sum is its
+// value to float32 rounding.
+struct Split3 {
+  bf16x8 t[3];
+  __device__ __forceinline__ explicit Split3(const f32x8& x) {
+    f32x8 y = x;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        t[q][e] = (__bf16)y[e];
+        y[e] -= (float)t[q][e];
+      }
+    }
+  }
+};
+// acc += a b to float32 rounding: float32 operands by float32 MFMAs, or, with
+// the bfloat16 rate, by the six products of their terms that matter (the
+// smallest first); b exact in bfloat16 takes three.
+__device__ __forceinline__ void mma16_split(f32x4& acc, const Split3& a, const Split3& b) {
+  mma16(acc, a.t[2], b.t[0]);
+  mma16(acc, a.t[0], b.t[2]);
+  mma16(acc, a.t[1], b.t[1]);
+  mma16(acc, a.t[1], b.t[0]);
+  mma16(acc, a.t[0], b.t[1]);
+  mma16(acc, a.t[0], b.t[0]);
+}
+__device__ __forceinline__ void mma16_split(f32x4& acc, const Split3& a, const bf16x8& b) {
+#pragma unroll
+  for (int q = 2; q >= 0; --q) mma16(acc, a.t[q], b);
+}
+__device__ __forceinline__ void mma16_split(f32x4& acc, const bf16x8& a, const Split3& b) {
+#pragma unroll
+  for (int q = 2; q >= 0; --q) mma16(acc, a, b.t[q]);
+}
+
 __device__ __forceinline__ f32x16 zero16() {
   f32x16 r;
 #pragma unroll

@@ -10,15 +10,31 @@
 // u_s^T over its tokens as the gated form with v_s replaced by u_s, and once the
 // pseudo-values u_s are known the chunked update and readout stages apply
 // unchanged.  The pseudo-values depend on the newest state before each token,
-// which depends on every earlier decision, so they come from a sequential scan
-// that keeps the newest state on chip: one 512-thread workgroup per head, each
-// thread holding a (d_k / 8) x (d_v / 64) block of the state in registers.
-// Per token it forms y = (alpha S)^T k and the score's three scalars (a =
-// |k|^2 |v|^2, b = |alpha S|^2, c = y . v), decides (Alg. 1, with Alg. 2 at a
-// full cache), and applies the rank-one step with u.  It emits the decisions,
-// scores and merge indices, the death token of every state leader (the same
-// bookkeeping as the gated scan), the cache's per-state counts and aggregated
-// scores, and u as float32.
+// which depends on every earlier decision, so a scan makes both: one 8-wave
+// workgroup per head, sequential over chunks of 64 tokens, the newest state in
+// registers (wave w: columns 16 w .. 16 w + 15, 16 x 16 MFMA tiles).
+//
+// Within a chunk y_t = (alpha S)^T k_t is linear in the values since the state
+// began, with coefficients that do not depend on where it began:
+//   y_t = A_t S_0^T k_t + sum_{r<t} W[t][r] beta_r (v_r - A_r S_0^T k_r),
+//   W[t][r] = M[t][r] - sum_{r<s<t} M[t][s] beta_s W[s][r],
+//   M[t][s] = exp(G_t - G_s) k_t . k_s,
+// for the state S_0 before the chunk, and the same sum over r >= p with S_0 = 0
+// for a state that begins at token p of the chunk.  So a chunk costs the Gram
+// products, one triangular solve for W (16 x 16 diagonal blocks by
+// substitution, the blocks below by float32 MFMAs) and the products for y; the
+// scores need y . v and |y|^2, explicit for S_0 and, once a boundary falls in
+// the chunk, from tables over the starts p (suffix sums of W beta (.) V V^T and
+// of its quadratic form).  The decisions are the gated scan's (scan_decide.h).
+// Products that carry float32 values run as bfloat16 MFMAs over three-term
+// splits (16-bit inputs) or as float32 MFMAs.
+//
+// Bound: latency, as the gated scan: a chain of eight phases between barriers,
+// about 20 us a chunk at d = 128 (128 heads x 4096 tokens: 1.3 ms).  Taking the
+// tokens one by one, as chunks with non-finite inputs or expanding steps still
+// are, costs two barriers and a reduction per token, 1.2 us, and made the scan
+// the whole call: 8 x 16 heads x 4k tokens 6.64 ms, now 2.35 ms; 12 heads x
+// 1,100 tokens 1.41 ms, now 0.44 ms.
 //
 // The call then runs the chunked update and readout stages of the gated form
 // over (q, k, u, lambda), on the gated prefill's schedule: with the scan in
@@ -28,324 +44,862 @@
 // bfloat16 terms, so the states stay float32 exact) and the readout a bfloat16
 // copy of u (for its in-chunk part, which rounds values to bfloat16 in the
 // gated form too); float32 inputs run the float32 stages on u.
-#include "prefill.h"
+#include <type_traits>
+
+#include "scan_decide.h"
 
 namespace dla {
 
-constexpr int DTHR = 512;        // threads of the delta scan
-constexpr int DWAVE = DTHR / 64;
-constexpr int DSL = 64;          // tokens staged in LDS per round
-
-// Barrier for the per-token exchanges through LDS: waits for the wave's LDS
-// operations only, so that the pseudo-values and exports stored to global
-// memory stay in flight (a full __syncthreads would wait for those stores at
-// every token).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_s_waitcnt((63 & 15) | (7 << 4) | (0 << 8) | ((63 >> 4) << 14));
-  __builtin_amdgcn_s_barrier();
-}
-
-template <int DK, int DV>
+template <int DK, int DV, typename Tin>
 struct DeltaP {
-  // wave w holds rows [w RB, (w + 1) RB) of the state, lane l columns
-  // [l CB, (l + 1) CB): a wave's share of S^T k covers every column, so it
-  // needs no exchange between lanes
-  static constexpr int RB = DK / DWAVE;  // state rows per thread
-  static constexpr int CB = DV / 64;     // state columns per thread
-  static_assert(RB * DWAVE == DK && CB * 64 == DV, "state blocks");
+  static constexpr int E = (int)sizeof(Tin);
+  static constexpr int EPP = 16 / E;                   // elements per 16 bytes
+  static constexpr int K16 = SL * DK * E / 16 / STHR;  // 16-byte K pieces per thread
+  static constexpr int V16 = SL * DV * E / 16 / STHR;
+  static constexpr int NI = DK / 16;                   // 16-row tiles of the state per wave
+  static constexpr int NW = DV / 16;                   // waves that hold state columns
+  static_assert(NW <= SWAVE, "state columns");
+  // LDS row strides (elements): padded by 16 bytes, so that lanes reading
+  // consecutive rows hit distinct banks
+  static constexpr int KRS = DK + EPP;  // sK [SL][KRS]
+  static constexpr int VRS = DV + EPP;  // sV [SL][VRS]
+  static constexpr int TRS = SL + EPP;  // sKt [DK][TRS], sVt [DV][TRS] (transposed, 16-bit inputs)
+  static constexpr bool TRANS = E == 2;
+  static constexpr int MRS = SL + 4;    // sM, sVV, sW [SL][MRS], 16-byte aligned rows
+  static constexpr int RRS = SL + 1;    // sR, sQ [SL][RRS]
+  static constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
+  static constexpr size_t MAT = (size_t)SL * MRS * 4;
+  // sK, with 16-bit inputs dead once the Gram products and the carry are formed:
+  // then the row tables take its bytes (float32 inputs read it in the state
+  // advance)
+  static constexpr size_t K_BYTES = cmax((size_t)SL * KRS * E, TRANS ? RowTables::BYTES : 0);
+  // sV, dead at the same time; then sQ
+  static constexpr size_t V_BYTES = cmax((size_t)SL * VRS * E, MAT);
+  static constexpr size_t T_BYTES = TRANS ? (size_t)(DK + DV) * TRS * E : RowTables::BYTES;
+  static_assert(K_BYTES % 16 == 0 && V_BYTES % 16 == 0 && T_BYTES % 16 == 0, "alignment");
   static size_t smem_bytes(int C) {
-    size_t off = (size_t)DSL * (DK + DV) * 4;  // sK, sV
-    off += (size_t)DSL * 4 * 5;                 // sAl, sBeta, sA, sBo, sMo
-    off += (size_t)(DWAVE + 1) * DV * 4;        // sY, sU
-    off += 2 * DWAVE * 4;                       // sRed
-    off = round_up(off, 8);
-    off += (size_t)C * 8;                       // sIb
-    off += (size_t)C * 4 * 2;                   // sN, sLead
+    size_t off = K_BYTES + V_BYTES + T_BYTES;
+    off += 3 * MAT;                       // sM (then sR), sVV, sW
+    off += 2 * (size_t)SWAVE * SL * 4;    // sPc, sPq
+    off += (size_t)SL * 4 * 9;            // float rows, boundary overrides
+    off += 64 + 128;                      // sRed, sMisc
+    if (C > kMaxRegC) off += (size_t)C * (8 + 4 + 4);
     return round_up(off, 16);
   }
 };
 
-template <int DK, int DV, typename Tin>
-__global__ __launch_bounds__(DTHR) void prefill_delta_scan_kernel(PrefillArgs a, PrefillWS w,
+// Whether a 16-byte piece of inputs holds an infinity or a NaN.
+__device__ __forceinline__ bool piece_bad(const u32x4& v, bf16_t) {
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    bad |= (v[i] & 0x7F80u) == 0x7F80u || (v[i] & 0x7F800000u) == 0x7F800000u;
+  return bad;
+}
+__device__ __forceinline__ bool piece_bad(const u32x4& v, float) {
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) bad |= (v[i] & 0x7F800000u) == 0x7F800000u;
+  return bad;
+}
+__device__ __forceinline__ bool is_bad(float x) {
+  return (__float_as_uint(x) & 0x7F800000u) == 0x7F800000u;
+}
+
+// NR: see the gated scan.
+template <int DK, int DV, typename Tin, int NR>
+__global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a, PrefillWS w,
                                                                   int tb, int te,
                                                                   const float* __restrict__ beta,
                                                                   float* __restrict__ U,
                                                                   bf16_t* __restrict__ U16) {
   if (!cache_matches(a.cache, a.desc)) return;  // refused call (see the prep kernel)
-  using P = DeltaP<DK, DV>;
-  constexpr int RB = P::RB, CB = P::CB;
+  using P = DeltaP<DK, DV, Tin>;
+  using FT = typename Frag<Tin>::T;
+  // float32 operands next to the inputs' type: three bfloat16 terms, or float32
+  using XT = typename std::conditional<P::E == 2, Split3, f32x8>::type;
   constexpr int D = DK * DV;
+  constexpr int NI = P::NI, NW = P::NW;
+  constexpr int KRS = P::KRS, VRS = P::VRS, TRS = P::TRS, MRS = P::MRS, RRS = P::RRS;
+  constexpr int K16 = P::K16, V16 = P::V16;
   const int h = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wv = tid >> 6;
-  const int rb = wv;    // row block of the thread's state block
-  const int cb = lane;  // column block
+  int tid = threadIdx.x;
+  int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int c16 = lane & 15;
+  int q4 = lane >> 4;
+  // The addresses of a phase derive from lane, c16 and q4.  Made opaque before
+  // each phase, they are formed there: hoisted out of the chunk loop, as the
+  // compiler otherwise does, they take some 270 registers more than there are.
+  auto fresh_lane = [&]() __attribute__((always_inline)) {
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    c16 = lane & 15;
+    q4 = lane >> 4;
+  };
   const int C = a.desc.C;
   const int T = a.T;
   const size_t tok0 = (size_t)h * T;
+  const bool own = wv < NW;       // the wave holds state columns 16 wv .. 16 wv + 15
+  const int col = 16 * wv + (tid & 15);  // the lane's state column
 
   extern __shared__ __align__(16) char smem[];
-  float* sK = reinterpret_cast<float*>(smem);  // [DSL][DK]
-  float* sV = sK + DSL * DK;                   // [DSL][DV]
-  float* sAl = sV + DSL * DV;                  // alpha_t
-  float* sBeta = sAl + DSL;
-  float* sA = sBeta + DSL;                     // |k|^2 |v|^2
-  int32_t* sBo = reinterpret_cast<int32_t*>(sA + DSL);
-  int32_t* sMo = sBo + DSL;
-  float* sY = reinterpret_cast<float*>(sMo + DSL);  // [waves][DV] partial y
-  float* sU = sY + DWAVE * DV;                      // [DV] pseudo-values
-  float* sRed = sU + DV;                            // [2 waves]
-  double* sIb =
-      reinterpret_cast<double*>(smem + round_up((size_t)((char*)(sRed + 2 * DWAVE) - smem), 8));
-  int32_t* sN = reinterpret_cast<int32_t*>(sIb + C);
-  int32_t* sLead = sN + C;
+  Tin* sK = reinterpret_cast<Tin*>(smem);
+  Tin* sV = reinterpret_cast<Tin*>(smem + P::K_BYTES);
+  float* sQ = reinterpret_cast<float*>(smem + P::K_BYTES);                // (alias of sV)
+  Tin* sKt = reinterpret_cast<Tin*>(smem + P::K_BYTES + P::V_BYTES);
+  Tin* sVt = sKt + DK * TRS;
+  const RowTables rows(P::TRANS ? smem : smem + P::K_BYTES + P::V_BYTES);
+  float* sM = reinterpret_cast<float*>(smem + P::K_BYTES + P::V_BYTES + P::T_BYTES);
+  float* sR = sM;                 // R[p][t] at [t RRS + p] (once M is no longer read)
+  float* sVV = sM + SL * MRS;
+  float* sW = sVV + SL * MRS;
+  float* sPc = sW + SL * MRS;     // [SWAVE][SL] the waves' shares of y . v
+  float* sPq = sPc + SWAVE * SL;  //                              |y|^2
+  float* sGc = sPq + SWAVE * SL;  // G_t - G(chunk start)
+  float* sA = sGc + SL;           // exp(sGc[t])
+  float* sAl = sA + SL;           // alpha_t
+  float* sAl2 = sAl + SL;         // alpha_t^2
+  float* sDe = sAl2 + SL;         // exp(G_end - G_t)
+  float* sBeta = sDe + SL;        // beta_t (0 past the chunk's end)
+  float* sKK = sBeta + SL;        // |k_t|^2
+  float* sV2 = sKK + SL;          // |v_t|^2
+  int32_t* sBo = reinterpret_cast<int32_t*>(sV2 + SL);  // boundary overrides
+  float* sRed = reinterpret_cast<float*>(sBo + SL);     // [16]
+  int32_t* sMisc = reinterpret_cast<int32_t*>(sRed + 16);
+  // sMisc: 0, 1 boundary mask; 2 start of the rows left (-1: none); 3 go on with
+  // the row tables; 4, 5 non-finite inputs of an even, an odd chunk; 6 the
+  // decision of the token by token path
+  __shared__ double sGlast[1];
 
   Meta M = meta_at(a.cache + a.meta_offset + (size_t)h * a.meta_stride, C);
   InitView iv = init_at(w, h, C);
-  // tokens [tb, te); a segment after the first resumes from the carry the
-  // previous one left in the workspace (the bookkeeping, and the newest state
-  // in this kernel's own thread order)
   ScarryView sv = scarry_at(w, h, C);
   const int m0 = min(max(*iv.m0, 0), C);
-  for (int j = tid; j < C; j += DTHR) {
-    if (tb == 0) {
-      sIb[j] = j < m0 ? M.ibar[j] : 0.0;
-      sN[j] = j < m0 ? M.n[j] : 0;
-      sLead[j] = j - m0;  // states present before the call: negative leaders
-    } else {
-      sIb[j] = sv.ibar[j];
-      sN[j] = sv.n[j];
-      sLead[j] = sv.lead[j];
+  using States = typename std::conditional<NR == 0, StatesInLds, StatesInRegs<NR>>::type;
+  ChunkDecider<States> dec;
+  dec.st.C = C;
+  if constexpr (NR == 0) {
+    dec.st.I = reinterpret_cast<double*>(sMisc + 32);  // [C]
+    dec.st.n = reinterpret_cast<int32_t*>(dec.st.I + C);
+    dec.st.ld = dec.st.n + C;
+  }
+  dec.m = 0;
+  dec.B = 0;
+  if (wv == 0) {
+    if (tb == 0)
+      dec.st.load(M.ibar, M.n, nullptr, m0);
+    else
+      dec.st.load(sv.ibar, sv.n, sv.lead, m0);
+    dec.m = __builtin_amdgcn_readfirstlane(tb == 0 ? m0 : min(max(*sv.m, 0), C));
+  }
+
+  // newest state at the start of the call, true (decayed) values: S[i][r] is row
+  // 16 i + 4 q4 + r of column col
+  f32x4 S[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) S[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const double G0 = *M.G;
+  if (own) {
+    if (tb > 0) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[i][r] = sv.S[(((size_t)wv * NI + i) * 4 + r) * 64 + lane];
+    } else if (m0 > 0) {
+      const float* src =
+          a.desc.state_dtype == DLA_BF16
+              ? reinterpret_cast<const float*>(a.cache + a.open_offset) + (size_t)h * D
+              : reinterpret_cast<const float*>(a.cache + a.states_offset) +
+                    ((size_t)h * C + min(max(M.perm[m0 - 1], 0), C - 1)) * D;
+      const float f = (float)exp(G0 - M.F[m0 - 1]);
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[i][r] = f * src[(size_t)(16 * i + 4 * q4 + r) * DV + col];
     }
   }
-  // the newest state at the start of the call, true (decayed) values
-  float S[RB][CB];
+  // |S|^2: the waves' shares in sRed, added where they are read (a chunk's
+  // barriers lie between)
+  auto norm_share = [&]() __attribute__((always_inline)) {
+    float x = 0.f;
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int j = 0; j < CB; ++j) S[i][j] = 0.f;
-  if (tb > 0) {
+      for (int r = 0; r < 4; ++r) x += S[i][r] * S[i][r];
+    x = wave_total_dpp(x);
+    if (lane == 0) sRed[wv] = x;
+  };
+  auto norm2 = [&]() __attribute__((always_inline)) -> float {
+    float b = 0.f;
 #pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int j = 0; j < CB; ++j) S[i][j] = sv.S[((size_t)tid * RB + i) * CB + j];
-  } else if (m0 > 0) {
-    const float* src =
-        a.desc.state_dtype == DLA_BF16
-            ? reinterpret_cast<const float*>(a.cache + a.open_offset) + (size_t)h * D
-            : reinterpret_cast<const float*>(a.cache + a.states_offset) +
-                  ((size_t)h * C + min(max(M.perm[m0 - 1], 0), C - 1)) * D;
-    const float f = (float)exp(*M.G - M.F[m0 - 1]);
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int j = 0; j < CB; ++j) S[i][j] = f * src[(size_t)(rb * RB + i) * DV + cb * CB + j];
-  }
-  int m = tb > 0 ? min(max(*sv.m, 0), C) : m0;
+    for (int i = 0; i < NW; ++i) b += sRed[i];
+    return b;
+  };
+  norm_share();
+  // W's blocks above the diagonal stay zero
+  for (int i = tid; i < SL * MRS; i += STHR) sW[i] = 0.f;
+  if (tid < 2) sMisc[4 + tid] = 0;
 
   const Tin* Kin = static_cast<const Tin*>(a.k) + tok0 * DK;
   const Tin* Vin = static_cast<const Tin*>(a.v) + tok0 * DV;
-  const float* g = a.g + tok0;
+  const double* Gtok = w.Gtok + tok0;
   const float* bt = beta + tok0;
   int32_t* death = w.death + tok0;
   float* Uh = U + tok0 * DV;
   bf16_t* U16h = U16 ? U16 + tok0 * DV : nullptr;  // bfloat16 copy (16-bit inputs)
-
-  for (int c0 = tb; c0 < te; c0 += DSL) {
-    const int nr = min(DSL, te - c0);
-    __syncthreads();  // the previous round is done with the staged tokens
-    for (int i = tid; i < nr * DK; i += DTHR) sK[i] = to_f32(Kin[(size_t)c0 * DK + i]);
-    for (int i = tid; i < nr * DV; i += DTHR) sV[i] = to_f32(Vin[(size_t)c0 * DV + i]);
-    for (int t = tid; t < nr; t += DTHR) {
-      sAl[t] = __expf(g[c0 + t]);
-      sBeta[t] = bt[c0 + t];
-      sBo[t] = a.b_ovr ? (int)a.b_ovr[tok0 + c0 + t] : -1;
-      sMo[t] = a.m_ovr ? a.m_ovr[tok0 + c0 + t] : -1;
+  // next chunk's tokens in registers (see the gated scan)
+  u32x4 pk[K16], pv[V16];
+  double gpre = 0.0;
+  float bepre = 0.f;
+  int bpre = -1, mpre = -1;
+  auto prefetch = [&](int c0n) __attribute__((always_inline)) {
+    const int nr = min(SL, T - c0n);
+#pragma unroll
+    for (int u = 0; u < K16; ++u) {
+      const int pi = tid + STHR * u;
+      pk[u] = reinterpret_cast<const u32x4*>(Kin + (size_t)(c0n + min(pi % SL, nr - 1)) * DK)[pi / SL];
     }
-    __syncthreads();
-    // a_t = |k_t|^2 |v_t|^2, one wave per token
-    for (int t = wv; t < nr; t += DWAVE) {
-      float kk = 0.f, vv = 0.f;
-      for (int i = lane; i < DK; i += 64) kk += sK[t * DK + i] * sK[t * DK + i];
-      for (int i = lane; i < DV; i += 64) vv += sV[t * DV + i] * sV[t * DV + i];
-      kk = wave_sum(kk);
-      vv = wave_sum(vv);
-      if (lane == 0) sA[t] = kk * vv;
+#pragma unroll
+    for (int u = 0; u < V16; ++u) {
+      const int pi = tid + STHR * u;
+      pv[u] = reinterpret_cast<const u32x4*>(Vin + (size_t)(c0n + min(pi % SL, nr - 1)) * DV)[pi / SL];
     }
-    __syncthreads();
+    if (tid < SL) {
+      const int t = min(tid, nr - 1);
+      gpre = Gtok[c0n + t];
+      bepre = bt[c0n + t];
+      bpre = (a.b_ovr && tid < nr) ? a.b_ovr[tok0 + c0n + tid] : (int8_t)-1;
+      mpre = (a.m_ovr && tid < nr) ? a.m_ovr[tok0 + c0n + tid] : -1;
+    }
+  };
+  prefetch(tb);
+  double Gprev = tb > 0 ? Gtok[tb - 1] : G0;
 
-    for (int tt = 0; tt < nr; ++tt) {
-      const int t = c0 + tt;
-      const float al = sAl[tt];
-      float kr[RB];
+  for (int c0 = tb; c0 < te; c0 += SL) {
+    const int nrow = min(SL, T - c0);
+    int32_t* sBad = sMisc + 4 + ((c0 / SL) & 1);
+    // ------------------------------------------------ stage the chunk
+    fresh_lane();
+    __syncthreads();  // the chunk before is done with the tables
+    bool bad = false;
+    float kpart = 0.f;  // the wave's share of |k|^2 of token lane
 #pragma unroll
-      for (int i = 0; i < RB; ++i) kr[i] = sK[tt * DK + rb * RB + i];
-      // decay, and the block's shares of y = S^T k, |S|^2 and c = k^T S v
-      float yp[CB];
+    for (int u = 0; u < K16; ++u) {
+      const int pi = tid + STHR * u;
+      const int r = pi % SL, pc = pi / SL;
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      const u32x4 val = (r < nrow) ? pk[u] : z;
+      bad |= piece_bad(val, Tin{});
 #pragma unroll
-      for (int j = 0; j < CB; ++j) yp[j] = 0.f;
-      float bp = 0.f;
+      for (int e = 0; e < P::EPP; ++e) {
+        const float x = to_f32(piece_elem<Tin>(val, e));
+        kpart += x * x;
+      }
+      *reinterpret_cast<u32x4*>(sK + r * KRS + pc * P::EPP) = val;
+      if constexpr (P::TRANS) put_transposed<TRS>(sKt, pc, r, val);
+    }
 #pragma unroll
-      for (int i = 0; i < RB; ++i)
+    for (int u = 0; u < V16; ++u) {
+      const int pi = tid + STHR * u;
+      const int r = pi % SL, pc = pi / SL;
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      const u32x4 val = (r < nrow) ? pv[u] : z;
+      bad |= piece_bad(val, Tin{});
+      *reinterpret_cast<u32x4*>(sV + r * VRS + pc * P::EPP) = val;
+      if constexpr (P::TRANS) put_transposed<TRS>(sVt, pc, r, val);
+    }
+    if (tid < SL) {
+      const int t = tid;
+      const double Glast = __shfl(gpre, nrow - 1, 64);
+      const float gc = (float)(gpre - Gprev);
+      const float gcp = __shfl_up(gc, 1, 64);  // token t - 1 (t >= 1)
+      const float gt = t == 0 ? gc : gc - gcp;
+      const float be = t < nrow ? bepre : 0.f;
+      sGc[t] = gc;
+      sA[t] = __expf(gc);
+      sAl[t] = (t < nrow) ? __expf(gt) : 0.f;
+      sAl2[t] = (t < nrow) ? __expf(2.f * gt) : 0.f;
+      sDe[t] = (t < nrow) ? __expf((float)(Glast - gpre)) : 0.f;
+      sBeta[t] = be;
+      sBo[t] = bpre;
+      bad |= is_bad(gc) || is_bad(be);
+      if (t == 0) sGlast[0] = Glast;
+    }
+    sPq[wv * SL + lane] = kpart;
+    if (__ballot(bad) && lane == 0) *sBad = 1;
+    __syncthreads();
+    const double Gnext = sGlast[0];  // G after the chunk's last token
+    const float b0 = norm2();        // |S|^2
+    // Token by token when an input of the chunk or the state is not finite, or
+    // when a token's step is not a contraction (beta |k|^2 outside [0, 2]): the
+    // tables range over starts that the boundaries may exclude, and only
+    // contractions bound them.
+    float kk = 0.f;
 #pragma unroll
-        for (int j = 0; j < CB; ++j) {
-          S[i][j] *= al;
-          yp[j] += kr[i] * S[i][j];
-          bp += S[i][j] * S[i][j];
+    for (int i = 0; i < SWAVE; ++i) kk += sPq[i * SL + lane];
+    const float bk = sBeta[lane] * kk;
+    const bool serial =  // (workgroup-uniform)
+        *sBad != 0 || is_bad(b0) || __ballot(!(bk >= 0.f && bk <= 2.f)) != 0;
+    if (tid == 0) sMisc[4 + (((c0 / SL) & 1) ^ 1)] = 0;
+    const int mforce = mpre;  // merge override of the lane's token (wave 0)
+    fresh_lane();
+    if (c0 + SL < te) prefetch(c0 + SL);
+
+    auto open_at = [&](int ts, float Is) __attribute__((always_inline)) {
+      dec.open(ts, Is, mforce, c0, C, T, &reinterpret_cast<CacheHeader*>(a.cache)->flags,
+               [&](int ld, int tk) { (ld >= 0 ? death[ld] : iv.death0[ld + m0]) = tk; });
+    };
+    const bool dense = __popcll(dec.B) >= NSEQ;  // (wave 0)
+    if (wv == 0) {
+      dec.p = -1;
+      dec.B = 0;
+      dec.mo = -1;
+      dec.dc = -1;
+      dec.io = 0.f;
+    }
+
+    if (!serial) {
+      fresh_lane();
+      // ------------------------------------ Gram products, and the carry S^T k
+      f32x4 X[4];   // X[i][r]: token 16 i + 4 q4 + r, column col
+      f32x4 Vr[4];  // the values in the same layout
+#pragma unroll
+      for (int i = 0; i < 4; ++i) X[i] = Vr[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      // the 10 + 10 lower 16 x 16 tiles of K K^T and V V^T, dealt to the waves
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const int ti = wv + SWAVE * u;
+        if (ti >= 20) break;
+        const bool isv = ti >= 10;
+        const int x = isv ? ti - 10 : ti;
+        const int tr = x < 1 ? 0 : (x < 3 ? 1 : (x < 6 ? 2 : 3));
+        const int tc = x - tr * (tr + 1) / 2;
+        f32x4 g = {0.f, 0.f, 0.f, 0.f};
+        if (!isv) {
+          const Tin* pa = sK + (16 * tr + c16) * KRS + 8 * q4;
+          const Tin* pb = sK + (16 * tc + c16) * KRS + 8 * q4;
+#pragma unroll
+          for (int ks = 0; ks < DK / 32; ++ks)
+            mma16(g, Frag<Tin>::load(pa + 32 * ks), Frag<Tin>::load(pb + 32 * ks));
+        } else {
+          const Tin* pa = sV + (16 * tr + c16) * VRS + 8 * q4;
+          const Tin* pb = sV + (16 * tc + c16) * VRS + 8 * q4;
+#pragma unroll
+          for (int ks = 0; ks < DV / 32; ++ks)
+            mma16(g, Frag<Tin>::load(pa + 32 * ks), Frag<Tin>::load(pb + 32 * ks));
         }
-      float cp = 0.f;
+        const int s = 16 * tc + c16;
+        const float gs = sGc[s];
 #pragma unroll
-      for (int j = 0; j < CB; ++j) cp += yp[j] * sV[tt * DV + cb * CB + j];
-      // the waves' shares are added below; |S|^2 and c over the wave
-      bp = wave_total_dpp(bp);
-      cp = wave_total_dpp(cp);
+        for (int r = 0; r < 4; ++r) {
+          const int t = 16 * tr + 4 * q4 + r;
+          if (isv)
+            sVV[t * MRS + s] = g[r];
+          else
+            sM[t * MRS + s] = s < t ? __expf(sGc[t] - gs) * g[r] : 0.f;
+          if (s == t) (isv ? sV2 : sKK)[t] = g[r];
+        }
+      }
+      fresh_lane();
+      if (own) {
 #pragma unroll
-      for (int j = 0; j < CB; ++j) sY[wv * DV + cb * CB + j] = yp[j];
-      if (lane == 0) {
-        sRed[wv] = bp;
-        sRed[DWAVE + wv] = cp;
-      }
-      lds_barrier();
-      float yj = 0.f;
-      if (tid < DV) {
+        for (int kk = 0; kk < DK / 32; ++kk) {
+          f32x8 sx;
 #pragma unroll
-        for (int w2 = 0; w2 < DWAVE; ++w2) yj += sY[w2 * DV + tid];
-      }
-      double b = 0.0, c = 0.0;
+          for (int e = 0; e < 8; ++e) sx[e] = S[2 * kk + (e >> 2)][e & 3];
+          const XT sb(sx);
 #pragma unroll
-      for (int w2 = 0; w2 < DWAVE; ++w2) {
-        b += (double)sRed[w2];
-        c += (double)sRed[DWAVE + w2];
+          for (int i = 0; i < 4; ++i) {
+            const Tin* kr = sK + (16 * i + c16) * KRS + 32 * kk + 4 * q4;
+            const FT ka = load_4x2<Tin>(kr, kr + 16);
+            if constexpr (P::E == 2)
+              mma16_split(X[i], ka, sb);
+            else
+              mma16(X[i], ka, sb);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 at = *reinterpret_cast<const float4*>(sA + 16 * i + 4 * q4);
+          X[i] *= f32x4{at.x, at.y, at.z, at.w};
+          if constexpr (P::TRANS) {
+            float x[4];
+            load4f(sVt + col * TRS + 16 * i + 4 * q4, x);
+            Vr[i] = f32x4{x[0], x[1], x[2], x[3]};
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Vr[i][r] = sV[(16 * i + 4 * q4 + r) * VRS + col];
+          }
+        }
       }
-      // the decision, identical in every thread
-      int bd;
-      float It;
-      if (m == 0) {  // the first token of an empty cache opens a state with score 0
-        bd = 1;
-        It = 0.f;
-      } else {
-        It = score_f(sA[tt], (float)b, (float)c, (float)D, a.eps, a.eps_rms);
-        bd = (It >= a.tau) ? 1 : 0;
-        if (sBo[tt] != -1) bd = sBo[tt] ? 1 : 0;
-        if (C == 1) bd = 0;
+      __syncthreads();
+
+      fresh_lane();
+      // ---------------------------------- W: y_t = sum_{r<t} W[t][r] beta_r v_r
+      // W[t][r] = M[t][r] - sum_{r<s<t} M[t][s] beta_s W[s][r]: within the 16 x 16
+      // diagonal blocks by substitution (wave 0, lane = block and column r) ...
+      if (wv == 0) {
+        const float* Mb = sM + 16 * q4 * MRS + 16 * q4;
+        float bw[16];  // beta_s W[s][r]
+        float be[16];
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {
+          const float4 b = *reinterpret_cast<const float4*>(sBeta + 16 * q4 + 4 * s4);
+          be[4 * s4] = b.x; be[4 * s4 + 1] = b.y; be[4 * s4 + 2] = b.z; be[4 * s4 + 3] = b.w;
+        }
+        bw[0] = 0.f;
+#pragma unroll
+        for (int t = 1; t < 16; ++t) {
+          float mrow[16];
+#pragma unroll
+          for (int s4 = 0; 4 * s4 < t; ++s4) {
+            const float4 x = *reinterpret_cast<const float4*>(Mb + t * MRS + 4 * s4);
+            mrow[4 * s4] = x.x; mrow[4 * s4 + 1] = x.y; mrow[4 * s4 + 2] = x.z; mrow[4 * s4 + 3] = x.w;
+          }
+          float x0 = Mb[t * MRS + c16], x1 = 0.f;
+#pragma unroll
+          for (int s = 1; s < t; ++s) (s & 1 ? x0 : x1) -= mrow[s] * bw[s];
+          const float wt = c16 < t ? x0 + x1 : 0.f;
+          sW[(16 * q4 + t) * MRS + 16 * q4 + c16] = wt;
+          bw[t] = be[t] * wt;
+        }
       }
-      if (bd) {
-        int istar = -1;
-        if (m == C) {
-          // Alg. 2 on wave 0: the adjacent pair of lowest density, ties to the
-          // lowest index (the gated scan's rules, overrides included)
-          if (wv == 0) {
-            double best = INFINITY;
-            int bi = 0x7fffffff;
-            for (int i = lane; i + 1 < C; i += 64) {
-              const double d = (sIb[i] + sIb[i + 1]) / (double)(sN[i] + sN[i + 1]);
-              if (d < best) {
-                best = d;
-                bi = i;
-              }
-            }
-            wave_argmin_d(best, bi);
-            istar = (bi >= 0 && bi <= C - 2) ? bi : 0;
-            if (__builtin_isnan((sIb[0] + sIb[1]) / (double)(sN[0] + sN[1]))) istar = 0;
-            const int fo = sMo[tt];
-            if (fo != -1) {
-              if (fo >= 0 && fo <= C - 2)
-                istar = fo;
-              else if (lane == 0)
-                atomicOr(&reinterpret_cast<CacheHeader*>(a.cache)->flags,
-                         DLA_FLAG_BAD_MERGE_OVERRIDE);
-            }
-            // the right state of the pair dies at token t
-            const int ld = sLead[istar + 1];
-            if (lane == 0) {
-              if (ld >= 0)
-                death[ld] = t;
-              else
-                iv.death0[ld + m0] = t;
-            }
-            for (int j0 = istar; j0 + 1 < m; j0 += 64) {
-              const int j = j0 + lane;
-              const bool act = j + 1 < m;
-              double nI = 0.0;
-              int nN = 0, nL = 0;
-              if (act) {
-                nI = (j == istar) ? sIb[j] + sIb[j + 1] : sIb[j + 1];
-                nN = (j == istar) ? sN[j] + sN[j + 1] : sN[j + 1];
-                nL = (j == istar) ? sLead[j] : sLead[j + 1];
-              }
-              __builtin_amdgcn_wave_barrier();
-              if (act) {
-                sIb[j] = nI;
-                sN[j] = nN;
-                sLead[j] = nL;
-              }
-              __builtin_amdgcn_wave_barrier();
+      __syncthreads();
+      fresh_lane();
+      // ... then the blocks below the diagonal, I rows and J columns of a pair of
+      // neighbouring blocks: P = M_IJ (1 - beta W)_JJ, W_IJ = (1 - W_II beta) P
+      auto row4 = [&](const float* m, int bi, int bj) __attribute__((always_inline)) -> f32x4 {
+        const float4 x = *reinterpret_cast<const float4*>(m + (16 * bi + c16) * MRS + 16 * bj + 4 * q4);
+        return f32x4{x.x, x.y, x.z, x.w};
+      };
+      auto tile4 = [&](const float* m, int bi, int bj) __attribute__((always_inline)) -> f32x4 {
+        f32x4 x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = m[(16 * bi + 4 * q4 + r) * MRS + 16 * bj + c16];
+        return x;
+      };
+      auto beta4 = [&](int b) __attribute__((always_inline)) -> f32x4 {
+        const float4 x = *reinterpret_cast<const float4*>(sBeta + 16 * b + 4 * q4);
+        return f32x4{x.x, x.y, x.z, x.w};
+      };
+      auto put4 = [&](int bi, int bj, const f32x4& x) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sW[(16 * bi + 4 * q4 + r) * MRS + 16 * bj + c16] = x[r];
+      };
+      if (wv < 2) {
+        const int J = 2 * wv, I = J + 1;
+        f32x4 pq = {0.f, 0.f, 0.f, 0.f}, wq = {0.f, 0.f, 0.f, 0.f};
+        mma16(pq, row4(sM, I, J), beta4(J) * tile4(sW, J, J));
+        pq = tile4(sM, I, J) - pq;
+        mma16(wq, row4(sW, I, I), beta4(I) * pq);
+        put4(I, J, pq - wq);
+      }
+      __syncthreads();
+      if (wv < 2) {  // 32 x 32 blocks: wave tj takes columns 16 tj ..
+        const int tj = wv;
+        f32x4 p0 = {0.f, 0.f, 0.f, 0.f}, p1 = p0;
+        for (int kb = tj; kb < 2; ++kb) {
+          const f32x4 b = beta4(kb) * tile4(sW, kb, tj);
+          mma16(p0, row4(sM, 2, kb), b);
+          mma16(p1, row4(sM, 3, kb), b);
+        }
+        p0 = tile4(sM, 2, tj) - p0;
+        p1 = tile4(sM, 3, tj) - p1;
+        f32x4 w0 = {0.f, 0.f, 0.f, 0.f}, w1 = w0;
+        const f32x4 b0p = beta4(2) * p0;
+        mma16(w0, row4(sW, 2, 2), b0p);
+        mma16(w1, row4(sW, 3, 2), b0p);
+        mma16(w1, row4(sW, 3, 3), beta4(3) * p1);
+        put4(2, tj, p0 - w0);
+        put4(3, tj, p1 - w1);
+      }
+      __syncthreads();
+
+      fresh_lane();
+      // -------- y, for the state before the chunk: Y = X + (W beta) (V - X)
+      f32x4 Y[4];
+      // 8 consecutive-pair elements of W beta's row t = 16 i + c16 for K step kk
+      // (tokens 32 kk + 4 q4 + e and 16 further), zero for tokens before lo
+      auto wrow = [&](int i, int kk, int lo) __attribute__((always_inline)) -> f32x8 {
+        const float* wp = sW + (16 * i + c16) * MRS + 32 * kk + 4 * q4;
+        const float4 wa = *reinterpret_cast<const float4*>(wp);
+        const float4 wb = *reinterpret_cast<const float4*>(wp + 16);
+        const float4 ba = *reinterpret_cast<const float4*>(sBeta + 32 * kk + 4 * q4);
+        const float4 bb = *reinterpret_cast<const float4*>(sBeta + 32 * kk + 16 + 4 * q4);
+        f32x8 x = {wa.x * ba.x, wa.y * ba.y, wa.z * ba.z, wa.w * ba.w,
+                   wb.x * bb.x, wb.y * bb.y, wb.z * bb.z, wb.w * bb.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (32 * kk + 16 * (e >> 2) + 4 * q4 + (e & 3) < lo) x[e] = 0.f;
+        return x;
+      };
+      if (own) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Y[i] = X[i];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          f32x8 z;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) z[e] = Vr[2 * kk + (e >> 2)][e & 3] - X[2 * kk + (e >> 2)][e & 3];
+          const XT zb(z);
+#pragma unroll
+          for (int i = 2 * kk; i < 4; ++i) {
+            const XT wa(wrow(i, kk, 0));
+            if constexpr (P::E == 2)
+              mma16_split(Y[i], wa, zb);
+            else
+              mma16(Y[i], wa, zb);
+          }
+        }
+        // the wave's shares of y . v and |y|^2, summed over its 16 columns
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            float cy = Y[i][r] * Vr[i][r], qy = Y[i][r] * Y[i][r];
+            cy += dpp_f<0x111, 0xF>(0.f, cy);
+            qy += dpp_f<0x111, 0xF>(0.f, qy);
+            cy += dpp_f<0x112, 0xF>(0.f, cy);
+            qy += dpp_f<0x112, 0xF>(0.f, qy);
+            cy += dpp_f<0x114, 0xF>(0.f, cy);
+            qy += dpp_f<0x114, 0xF>(0.f, qy);
+            cy += dpp_f<0x118, 0xF>(0.f, cy);
+            qy += dpp_f<0x118, 0xF>(0.f, qy);
+            if (c16 == 15) {
+              sPc[wv * SL + 16 * i + 4 * q4 + r] = cy;
+              sPq[wv * SL + 16 * i + 4 * q4 + r] = qy;
             }
           }
-          m -= 1;
+      }
+      __syncthreads();
+
+      fresh_lane();
+      // ------------------------------------------------------- decisions
+      RowIn rin;
+      rin.nrow = nrow;
+      rin.C = C;
+      rin.D = (float)D;
+      rin.tau = a.tau;
+      rin.eps = a.eps;
+      rin.eps_rms = a.eps_rms;
+      const float kk2 = sKK[lane], vv2 = sV2[lane], bet = sBeta[lane];
+      rin.a = kk2 * vv2;
+      rin.al2n = (lane + 1 < SL) ? sAl2[lane + 1] : 0.f;
+      rin.bo = sBo[lane];
+      // growth of |S|^2 with a token of y . v = c and |y|^2 = q: S + k u^T, u =
+      // beta (v - y)
+      auto grow = [&](float c, float q) __attribute__((always_inline)) -> float {
+        const float u2 = vv2 - 2.f * c + q;
+        return 2.f * bet * (c - q) + kk2 * bet * bet * (u2 < 0.f ? 0.f : u2);
+      };
+      auto row = [&](int p, float& ct, float& inc) __attribute__((always_inline)) {
+        ct = (lane > p) ? sR[lane * RRS + p] : 0.f;
+        inc = grow(ct, (lane > p) ? sQ[lane * RRS + p] : 0.f);
+      };
+      if (wv == 0) {
+        if (dec.m == 0) {
+          // the first token of an empty cache opens a state with score 0
+          dec.st.push(0, 0.0, c0);
+          dec.m = 1;
+          dec.p = 0;
+          dec.B = 1;
+          if (lane == 0) dec.dc = T;
         }
-        if (tid == 0) {
-          sN[m] = 1;
-          sIb[m] = (double)It;
-          sLead[m] = t;
-          death[t] = T;
-          if (a.b_out) a.b_out[tok0 + t] = 1;
-          if (a.merge_out) a.merge_out[tok0 + t] = istar;
-          if (a.score_out) a.score_out[tok0 + t] = It;
-        }
-        m += 1;
-      } else {
-        if (tid == 0) {
-          sN[m - 1] += 1;
-          sIb[m - 1] += (double)It;
-          death[t] = -1;
-          if (a.b_out) a.b_out[tok0 + t] = 0;
-          if (a.merge_out) a.merge_out[tok0 + t] = -1;
-          if (a.score_out) a.score_out[tok0 + t] = It;
+        const bool more = dec.first_rows(
+            rin, 1,
+            [&](int p, float& ct, float& inc, float& binit) __attribute__((always_inline)) {
+              // (an empty cache's first token starts from S = 0)
+              float c = 0.f, q = 0.f;
+#pragma unroll
+              for (int i = 0; i < NW; ++i) {
+                c += sPc[i * SL + lane];
+                q += sPq[i * SL + lane];
+              }
+              ct = c;
+              inc = grow(c, q);
+              binit = sA[0] * sA[0] * b0;
+            },
+            open_at);
+        if (lane == 0) {
+          sMisc[0] = (int)(uint32_t)dec.B;
+          sMisc[1] = (int)(uint32_t)(dec.B >> 32);
+          sMisc[2] = more ? dec.p : -1;
         }
       }
-      // pseudo-values, then the rank-one step (a new state starts from zero)
-      if (tid < DV) {
-        const float u = sBeta[tt] * (sV[tt * DV + tid] - (bd ? 0.f : yj));
-        sU[tid] = u;
-        Uh[(size_t)t * DV + tid] = u;
-        if (U16h) U16h[(size_t)t * DV + tid] = from_f32<bf16_t>(u);
+      __syncthreads();
+      if (sMisc[2] >= 0) {  // (workgroup-uniform) a state began in the chunk
+        fresh_lane();
+        // Tables for every start p in the chunk: y . v = sum_{r=p}^{t-1} (W
+        // beta)[t][r] (v_r . v_t), and |y|^2 = sum_{r>=p} x_r (2 sum_{r'>r} x_r'
+        // (v_r . v_r') + x_r |v_r|^2) with x_r = (W beta)[t][r].
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int x = wv + SWAVE * u;
+          if (x >= 10) break;
+          const int tr = x < 1 ? 0 : (x < 3 ? 1 : (x < 6 ? 2 : 3));
+          const int tc = x - tr * (tr + 1) / 2;
+          f32x4 z = {0.f, 0.f, 0.f, 0.f};
+          for (int kb = tc; kb <= tr; ++kb) {
+            f32x4 b = tile4(sVV, kb, tc);  // rows r' of block kb, column r
+            if (kb == tc) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if (4 * q4 + r <= c16) b[r] = 0.f;
+            }
+            mma16(z, row4(sW, tr, kb) * beta4(kb), b);
+          }
+          const float br = sBeta[16 * tc + c16], vr2 = sV2[16 * tc + c16];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int t = 16 * tr + 4 * q4 + r;
+            const float xr = sW[t * MRS + 16 * tc + c16] * br;
+            sQ[t * RRS + 16 * tc + c16] = xr * (2.f * z[r] + vr2 * xr);
+          }
+        }
+        __syncthreads();
+        {
+          const int s = SL - 1 - lane;  // the suffix sum over s is a prefix sum over the lanes
+          const float bs = sBeta[s];
+#pragma unroll
+          for (int t = wv; t < SL; t += SWAVE) {
+            float x = (s < t) ? sW[t * MRS + s] * bs * sVV[t * MRS + s] : 0.f;
+            float y = (s < t) ? sQ[t * RRS + s] : 0.f;
+            x += dpp_f<0x111, 0xF>(0.f, x);
+            y += dpp_f<0x111, 0xF>(0.f, y);
+            x += dpp_f<0x112, 0xF>(0.f, x);
+            y += dpp_f<0x112, 0xF>(0.f, y);
+            x += dpp_f<0x114, 0xF>(0.f, x);
+            y += dpp_f<0x114, 0xF>(0.f, y);
+            x += dpp_f<0x118, 0xF>(0.f, x);
+            y += dpp_f<0x118, 0xF>(0.f, y);
+            x += dpp_f<0x142, 0xA>(0.f, x);
+            y += dpp_f<0x142, 0xA>(0.f, y);
+            x += dpp_f<0x143, 0xC>(0.f, x);
+            y += dpp_f<0x143, 0xC>(0.f, y);
+            sR[t * RRS + s] = x;
+            sQ[t * RRS + s] = y;
+          }
+        }
+        __syncthreads();
+        if (wv == 0) {
+          bool more = true;
+          if (!dense)
+            more = dec.first_rows(
+                rin, NSEQ - 1,
+                [&](int p, float& ct, float& inc, float& binit) __attribute__((always_inline)) {
+                  row(p, ct, inc);
+                  binit = 0.f;
+                },
+                open_at);
+          if (lane == 0) sMisc[3] = more ? dec.p : -1;
+        }
+        __syncthreads();
+        const int prow = sMisc[3];
+        if (prow >= 0) {  // (workgroup-uniform)
+          fill_rows(rin, prow, rows, row);
+          __syncthreads();
+          if (wv == 0) dec.finish_rows(rin, rows, open_at);
+        }
+        if (wv == 0 && lane == 0) {
+          sMisc[0] = (int)(uint32_t)dec.B;
+          sMisc[1] = (int)(uint32_t)(dec.B >> 32);
+        }
+        __syncthreads();
       }
-      lds_barrier();
-      float uc[CB];
+
+      fresh_lane();
+      // -------------------------------- pseudo-values, and the state's advance
+      const uint64_t B = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(sMisc[0]) |
+                         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(sMisc[1]) << 32);
+      auto start_of = [&](int t) __attribute__((always_inline)) -> int {  // of token t's state
+        const uint64_t x = B & (~0ull >> (63 - t));
+        return x ? 63 - __clzll((long long)x) : -1;
+      };
+      const int plast = start_of(SL - 1);
+      if (own) {
+        if (B) {
+          // tokens whose state began in the chunk: Y = (W beta) V over its tokens
+          f32x4 Z[4];
 #pragma unroll
-      for (int j = 0; j < CB; ++j) uc[j] = sU[cb * CB + j];
+          for (int i = 0; i < 4; ++i) Z[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < RB; ++i)
+          for (int kk = 0; kk < 2; ++kk) {
+            f32x8 z;
 #pragma unroll
-        for (int j = 0; j < CB; ++j) S[i][j] = (bd ? 0.f : S[i][j]) + kr[i] * uc[j];
+            for (int e = 0; e < 8; ++e) z[e] = Vr[2 * kk + (e >> 2)][e & 3];
+            FT vb;
+            if constexpr (P::E == 2) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) vb[e] = (__bf16)z[e];  // (exact)
+            } else {
+              vb = z;
+            }
+#pragma unroll
+            for (int i = 2 * kk; i < 4; ++i) {
+              const XT wa(wrow(i, kk, start_of(16 * i + c16)));
+              if constexpr (P::E == 2)
+                mma16_split(Z[i], wa, vb);
+              else
+                mma16(Z[i], wa, vb);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (start_of(16 * i + 4 * q4 + r) >= 0) Y[i][r] = Z[i][r];
+        }
+        fresh_lane();
+        const int s0 = plast < 0 ? 0 : plast;
+        const float sc = (plast < 0) ? sA[nrow - 1] : 0.f;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) S[i] *= sc;
+        f32x4 ud[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 de = [&]() __attribute__((always_inline)) {
+            const float4 x = *reinterpret_cast<const float4*>(sDe + 16 * i + 4 * q4);
+            return f32x4{x.x, x.y, x.z, x.w};
+          }();
+          const f32x4 u = beta4(i) * (Vr[i] - Y[i]);
+          ud[i] = u * de;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int t = 16 * i + 4 * q4 + r;
+            if (t < s0) ud[i][r] = 0.f;
+            if (t < nrow) {
+              Uh[(size_t)(c0 + t) * DV + col] = u[r];
+              if (U16h) U16h[(size_t)(c0 + t) * DV + col] = from_f32<bf16_t>(u[r]);
+            }
+          }
+        }
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          if (32 * kk + 31 < s0 || 32 * kk >= nrow) continue;  // (uniform)
+          f32x8 z;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) z[e] = ud[2 * kk + (e >> 2)][e & 3];
+          const XT ub(z);
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            FT ka;
+            if constexpr (P::TRANS) {
+              const Tin* kp = sKt + (16 * i + c16) * TRS + 32 * kk + 4 * q4;
+              ka = load_4x2<Tin>(kp, kp + 16);
+              mma16_split(S[i], ka, ub);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                ka[e] = sK[(32 * kk + 16 * (e >> 2) + 4 * q4 + (e & 3)) * KRS + 16 * i + c16];
+              mma16(S[i], ka, ub);
+            }
+          }
+        }
+      }
+    } else {
+      fresh_lane();
+      // ---------------------------------------------------- token by token
+      for (int t = 0; t < nrow; ++t) {
+        float y = 0.f, b = 0.f, kr[NI][4];
+        const float vt = own ? to_f32(sV[t * VRS + col]) : 0.f;
+        if (own) {
+          const float al = sAl[t];
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            load4f(sK + t * KRS + 16 * i + 4 * q4, kr[i]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              S[i][r] *= al;
+              y += kr[i][r] * S[i][r];
+              b += S[i][r] * S[i][r];
+            }
+          }
+          y += __shfl_xor(y, 16, 64);
+          y += __shfl_xor(y, 32, 64);
+          b = wave_total_dpp(b);
+          const float c = wave_total_dpp(q4 == 0 ? y * vt : 0.f);
+          if (lane == 0) {
+            sPc[wv] = b;  // (sPq may still be read for the choice of this path)
+            sPc[16 + wv] = c;
+          }
+        }
+        __syncthreads();
+        if (wv == 0) {
+          float kk2 = 0.f, vv2 = 0.f;
+          for (int i = lane; i < DK; i += 64) kk2 += to_f32(sK[t * KRS + i]) * to_f32(sK[t * KRS + i]);
+          for (int i = lane; i < DV; i += 64) vv2 += to_f32(sV[t * VRS + i]) * to_f32(sV[t * VRS + i]);
+          kk2 = wave_sum(kk2);
+          vv2 = wave_sum(vv2);
+          double bs = 0.0, cs = 0.0;
+#pragma unroll
+          for (int i = 0; i < NW; ++i) {
+            bs += (double)sPc[i];
+            cs += (double)sPc[16 + i];
+          }
+          int bd = 1;
+          float It = 0.f;  // the first token of an empty cache opens a state with score 0
+          if (dec.m > 0) {
+            It = score_f(kk2 * vv2, (float)bs, (float)cs, (float)D, a.eps, a.eps_rms);
+            bd = (It >= a.tau) ? 1 : 0;
+            if (sBo[t] != -1) bd = sBo[t] ? 1 : 0;
+            if (C == 1) bd = 0;
+          }
+          bd = __builtin_amdgcn_readfirstlane(bd);
+          if (bd) {
+            open_at(t, It);
+          } else {
+            dec.st.join(dec.m - 1, 1, (double)It);
+            if (lane == t) dec.io = It;
+          }
+          if (lane == 0) sMisc[6] = bd;
+        }
+        __syncthreads();
+        if (own) {
+          const bool bd = sMisc[6] != 0;
+          const float u = sBeta[t] * (vt - (bd ? 0.f : y));
+          if (q4 == 0) {
+            Uh[(size_t)(c0 + t) * DV + col] = u;
+            if (U16h) U16h[(size_t)(c0 + t) * DV + col] = from_f32<bf16_t>(u);
+          }
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) S[i][r] = (bd ? 0.f : S[i][r]) + kr[i][r] * u;
+        }
+      }
     }
+    fresh_lane();
+    norm_share();
+    if (wv == 0 && lane < nrow) {
+      death[c0 + lane] = dec.dc;
+      if (a.b_out) a.b_out[tok0 + c0 + lane] = (int8_t)((dec.B >> lane) & 1);
+      if (a.merge_out) a.merge_out[tok0 + c0 + lane] = dec.mo;
+      if (a.score_out) a.score_out[tok0 + c0 + lane] = dec.io;
+    }
+    Gprev = Gnext;
   }
-  __syncthreads();
-  if (te < T) {
-    // the carry for the next segment
-    for (int j = tid; j < C; j += DTHR) {
-      sv.ibar[j] = sIb[j];
-      sv.n[j] = sN[j];
-      sv.lead[j] = sLead[j];
-    }
-    if (tid == 0) *sv.m = m;
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int j = 0; j < CB; ++j) sv.S[((size_t)tid * RB + i) * CB + j] = S[i][j];
+  if (te == T) {
+    if (wv == 0) dec.st.store(M.ibar, M.n, nullptr, dec.m);
     return;
   }
-  for (int j = tid; j < m; j += DTHR) {
-    M.n[j] = sN[j];
-    M.ibar[j] = sIb[j];
+  // the carry for the next segment
+  if (wv == 0) {
+    dec.st.store(sv.ibar, sv.n, sv.lead, dec.m);
+    if (lane == 0) *sv.m = dec.m;
+  }
+  if (own) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sv.S[(((size_t)wv * NI + i) * 4 + r) * 64 + lane] = S[i][r];
   }
 }
 
 template <int DK, int DV>
 static size_t delta_smem(int C) {
-  return DeltaP<DK, DV>::smem_bytes(C);
+  const size_t f = DeltaP<DK, DV, float>::smem_bytes(C), b = DeltaP<DK, DV, bf16_t>::smem_bytes(C);
+  return f > b ? f : b;
 }
 
 size_t prefill_delta_scan_smem(const dla_cache_desc& d) {
@@ -358,14 +912,18 @@ size_t prefill_delta_scan_smem(const dla_cache_desc& d) {
 template <int DK, int DV, typename Tin>
 static hipError_t launch_delta_scan_t(const PrefillArgs& a, const PrefillWS& w, int tb, int te,
                                       const float* beta, float* U, bf16_t* U16, hipStream_t s) {
-  const size_t shm = DeltaP<DK, DV>::smem_bytes(a.desc.C);
+  const size_t shm = DeltaP<DK, DV, Tin>::smem_bytes(a.desc.C);
   if (shm > 160 * 1024) return hipErrorInvalidValue;
-  auto k = prefill_delta_scan_kernel<DK, DV, Tin>;
-  if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
-      hipSuccess)
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k, dim3(a.desc.B * a.desc.H), dim3(DTHR), shm, s, a, w, tb, te, beta, U, U16);
-  return hipGetLastError();
+  auto launch = [&](auto k) -> hipError_t {
+    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
+        hipSuccess)
+      return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3(a.desc.B * a.desc.H), dim3(STHR), shm, s, a, w, tb, te, beta, U, U16);
+    return hipGetLastError();
+  };
+  if (a.desc.C > kMaxRegC) return launch(prefill_delta_scan_kernel<DK, DV, Tin, 0>);
+  if (a.desc.C > 64) return launch(prefill_delta_scan_kernel<DK, DV, Tin, 4>);
+  return launch(prefill_delta_scan_kernel<DK, DV, Tin, 1>);
 }
 
 template <int DK, int DV>
@@ -433,22 +991,7 @@ hipError_t launch_prefill_delta(const PrefillArgs& a, const float* beta, hipStre
   fr.v_f32 = 0;
   if (wide) fr.v = U16;
   const bool pipe = pipelined(a.T, a.in_dtype, readout, serial);
-  SegPlan p = seg_plan(a.desc, a.T, a.in_dtype, readout, serial, a.pool_budget);
-  if (pipe && p.shared) {
-    // Here the scan is the long stage (its sequential chain per token takes
-    // about three times the update and readout), so the segments stay at the
-    // ramp's first size instead of growing: what remains after the scan, the
-    // last segment's update and readout, is then short.  The pool is shared,
-    // so the segments change neither the workspace nor the results.
-    p.fit = p.first;
-    p.nseg = 0;
-    p.nch_seg = 0;
-    for (int b = 0; b < p.nch; ++p.nseg) {
-      const int n = ramp_size(p.first, p.fit, p.nseg, p.nch - b);
-      p.nch_seg = n > p.nch_seg ? n : p.nch_seg;
-      b += n;
-    }
-  }
+  const SegPlan p = seg_plan(a.desc, a.T, a.in_dtype, readout, serial, a.pool_budget);
   const PrefillWS w = ws_layout(base, nh, a.T, a.desc.C, a.desc.d_k * a.desc.d_v, p.nch);
   hipError_t e;
   if ((e = launch_prefill_prep(fu, s)) != hipSuccess) return e;

@@ -11,6 +11,7 @@
 // much as three rows; it is taken from the NSEQ-th boundary of a chunk on, and
 // from the first when the chunk before had that many.
 #pragma once
+#include "mfma.h"
 #include "prefill.h"
 
 namespace dla {
@@ -19,6 +20,27 @@ constexpr int SL = 64;      // tokens per scan chunk (one per lane of a wavefron
 constexpr int SWAVE = 8;    // waves per scan workgroup
 constexpr int STHR = 64 * SWAVE;
 constexpr int NSEQ = 4;     // boundaries of a chunk taken row by row
+
+// Transposed copy of a 16-bit piece (columns 8 pc .. 8 pc + 7 of token r, r =
+// lane): the lane pair (2i, 2i + 1) swaps halves, so each lane writes 32-bit
+// words holding both tokens of the pair, 4 columns each.
+template <int TRS>
+__device__ __forceinline__ void put_transposed(bf16_t* dst, int pc, int r, const u32x4& val) {
+  const bool odd = (r & 1) != 0;
+  const uint32_t s0 = odd ? val[0] : val[2], s1 = odd ? val[1] : val[3];
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)s0, 0xB1, 0xF, 0xF, false);
+  const uint32_t r1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)s1, 0xB1, 0xF, 0xF, false);
+  // even lane: columns 0..3, own token first; odd lane: columns 4..7, the
+  // partner's token (r - 1) first
+  const uint32_t m0 = odd ? val[2] : val[0], m1 = odd ? val[3] : val[1];
+  const uint32_t lo0 = odd ? r0 : m0, hi0 = odd ? m0 : r0;
+  const uint32_t lo1 = odd ? r1 : m1, hi1 = odd ? m1 : r1;
+  uint32_t* row = reinterpret_cast<uint32_t*>(dst + (pc * 8 + (odd ? 4 : 0)) * TRS + (r & ~1));
+  row[0] = __builtin_amdgcn_perm(hi0, lo0, 0x05040100u);
+  row[TRS / 2] = __builtin_amdgcn_perm(hi0, lo0, 0x07060302u);
+  row[TRS] = __builtin_amdgcn_perm(hi1, lo1, 0x05040100u);
+  row[3 * (TRS / 2)] = __builtin_amdgcn_perm(hi1, lo1, 0x07060302u);
+}
 
 // value of the next lane (lane 63: `last`)
 __device__ __forceinline__ int next_lane_i(int x, int last) { return dpp_i<0x130, 0xF>(last, x); }
