@@ -47,26 +47,38 @@ typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 // NT: with the non-temporal hint.  (A template parameter, not a run-time
 // choice: a select between a hinted and a plain load of one address is folded
 // into one load without the hint.)
-template <bool NT>
-__device__ __forceinline__ float4 ld_group(const float* base, int g) {
-  const f32x4v* p = reinterpret_cast<const f32x4v*>(base) + g;
-  f32x4v x;
+template <bool NT, typename V>
+__device__ __forceinline__ V ld_vec(const V* p) {
   if constexpr (NT)
-    x = __builtin_nontemporal_load(p);
+    return __builtin_nontemporal_load(p);
   else
-    x = *p;
+    return *p;
+}
+// a group of 4 elements as stored, and widened to float32
+template <typename TS>
+struct Raw;
+template <>
+struct Raw<float> {
+  using T = f32x4v;
+};
+template <>
+struct Raw<bf16_t> {
+  using T = u32x2v;
+};
+template <bool NT, typename TS>
+__device__ __forceinline__ typename Raw<TS>::T ld_raw(const TS* base, int g) {
+  return ld_vec<NT>(reinterpret_cast<const typename Raw<TS>::T*>(base) + g);
+}
+__device__ __forceinline__ float4 widen(const f32x4v& x) {
   return make_float4(x[0], x[1], x[2], x[3]);
 }
-template <bool NT>
-__device__ __forceinline__ float4 ld_group(const bf16_t* base, int g) {
-  const u32x2v* p = reinterpret_cast<const u32x2v*>(base) + g;
-  u32x2v x;
-  if constexpr (NT)
-    x = __builtin_nontemporal_load(p);
-  else
-    x = *p;
+__device__ __forceinline__ float4 widen(const u32x2v& x) {
   return make_float4(__uint_as_float(x[0] << 16), __uint_as_float(x[0] & 0xFFFF0000u),
                      __uint_as_float(x[1] << 16), __uint_as_float(x[1] & 0xFFFF0000u));
+}
+template <bool NT, typename TS>
+__device__ __forceinline__ float4 ld_group(const TS* base, int g) {
+  return widen(ld_raw<NT>(base, g));
 }
 __device__ __forceinline__ void st_group(float* base, int g, const float4& v) {
   const f32x4v x = {v.x, v.y, v.z, v.w};
@@ -326,10 +338,34 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a) {
   float4 Sopen[ST::NV];
   float ct = 0.f, bt = 0.f;
   if (m > 0) {
+#pragma unroll
+    for (int r = 0; r < ST::NV; ++r) Sopen[r] = ld_group<!SPLIT>(newest, tid + 256 * r);
+  }
+  // A split step streams few states per workgroup, and its decisions (the time
+  // of some 15 states) would leave memory idle: the first closed state of the
+  // range is requested before them (behind the newest state, whose wait must
+  // not cover it), and each further one before the one at hand is used.
+  typename Raw<TS>::T nx[SPLIT ? ST::NV : 1];
+  auto request = [&](int j) __attribute__((always_inline)) {
+    const TS* src = states + (size_t)sP[j] * D;
+#pragma unroll
+    for (int r = 0; r < ST::NV; ++r) nx[r] = ld_raw<true>(src, tid + 256 * r);
+  };
+  int jreq = -1;  // the state requested
+  if constexpr (SPLIT) {
+    int p0, p1;
+    split_range(m, ns, sp, -1, &p0, &p1);
+    if (p0 < min(p1, m - 1)) {
+      __builtin_amdgcn_sched_barrier(0);
+      request(p0);
+      __builtin_amdgcn_sched_barrier(0);
+      jreq = p0;
+    }
+  }
+  if (m > 0) {
     const float4 vq = reinterpret_cast<const float4*>(sv)[cq];
 #pragma unroll
     for (int r = 0; r < ST::NV; ++r) {
-      Sopen[r] = ld_group<!SPLIT>(newest, tid + 256 * r);
       const float kr = sk[rg + ST::RG * r];
       const float4 s = Sopen[r];
       ct += kr * (s.x * vq.x + s.y * vq.y + s.z * vq.z + s.w * vq.w);
@@ -422,19 +458,11 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a) {
   int j0, j1;
   split_range(m, ns, sp, istar, &j0, &j1);
 
-  for (int j = j0; j < j1; ++j) {
-    const bool is_open = (j == m - 1);
-    float4 X[ST::NV];
-    if (is_open) {
-#pragma unroll
-      for (int r = 0; r < ST::NV; ++r) X[r] = Sopen[r];
-    } else {
-      const TS* src = states + (size_t)sP[j] * D;
-#pragma unroll
-      for (int r = 0; r < ST::NV; ++r) X[r] = ld_group<true>(src, tid + 256 * r);
-    }
-    const int post = (istar >= 0 && j > istar) ? j - 1 : j;
-    const float w = a.skip_readout ? 0.f : sLam[post] * __expf((float)(Gn - sF[j]));
+  // state j (after the merge in position post) read out with weight w
+  auto weight = [&](int j, int post) __attribute__((always_inline)) {
+    return a.skip_readout ? 0.f : sLam[post] * __expf((float)(Gn - sF[j]));
+  };
+  auto read_out = [&](const float4 (&X)[ST::NV], float w) __attribute__((always_inline)) {
     float y0 = 0.f, y1 = 0.f, y2 = 0.f, y3 = 0.f;
 #pragma unroll
     for (int r = 0; r < ST::NV; ++r) {
@@ -447,53 +475,104 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a) {
     o4[1] += w * y1;
     o4[2] += w * y2;
     o4[3] += w * y3;
+  };
+  // merged pair (X, Y) of states j, j + 1, stored in this step's frame Gn:
+  //   S~ = exp(Gn - F_i) S~_i + exp(Gn - F_{i+1}) S~_{i+1}.
+  // Gn is at least as recent as either frame, so both factors are <= 1.
+  // (The frame of the later state is not always the more recent one: the left
+  // state may have been rewritten by a merge after its neighbour was last
+  // written, and rebasing to the older frame can overflow.)
+  auto merge = [&](int j, const float4 (&X)[ST::NV], const float4 (&Y)[ST::NV])
+      __attribute__((always_inline)) {
+    const float e1 = __expf((float)(Gn - sF[j]));
+    const float e2 = __expf((float)(Gn - sF[j + 1]));
+    TS* dst = states + (size_t)sP[j] * D;
+#pragma unroll
+    for (int r = 0; r < ST::NV; ++r) {
+      float4 s;
+      s.x = e1 * X[r].x + e2 * Y[r].x;
+      s.y = e1 * X[r].y + e2 * Y[r].y;
+      s.z = e1 * X[r].z + e2 * Y[r].z;
+      s.w = e1 * X[r].w + e2 * Y[r].w;
+      st_group(dst, tid + 256 * r, s);
+    }
+  };
+  // the newest state closes: its bfloat16 copy goes to its slot, in its own
+  // frame (a merge with its left neighbour is handled apart)
+  auto close = [&](int j, const float4 (&X)[ST::NV]) __attribute__((always_inline)) {
+    TS* dst = states + (size_t)sP[j] * D;
+#pragma unroll
+    for (int r = 0; r < ST::NV; ++r) st_group(dst, tid + 256 * r, X[r]);
+  };
 
-    if (j == istar) {
-      // merged pair, stored in this step's frame Gn:
-      //   S~ = exp(Gn - F_i) S~_i + exp(Gn - F_{i+1}) S~_{i+1}.
-      // Gn is at least as recent as either frame, so both factors are <= 1.
-      // (The frame of the later state is not always the more recent one: the
-      // left state may have been rewritten by a merge after its neighbour was
-      // last written, and rebasing to the older frame can overflow.)
-      const int j2 = j + 1;
-      float4 Y[ST::NV];
-      if (j2 == m - 1) {
+  if constexpr (SPLIT) {
+    // the newest state, when the range holds it, is read again (from L2): its
+    // registers hold the requested state here
+    auto reopen = [&](float4 (&X)[ST::NV]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < ST::NV; ++r) Y[r] = Sopen[r];
+      for (int r = 0; r < ST::NV; ++r) X[r] = ld_group<false>(newest, tid + 256 * r);
+    };
+    const int je = min(j1, m - 1);  // end of the range's closed states
+    int j = j0;
+    if (j < je && j != jreq) request(j);
+    while (j < je) {
+      float4 X[ST::NV];
+#pragma unroll
+      for (int r = 0; r < ST::NV; ++r) X[r] = widen(nx[r]);
+      const bool pair = j == istar;
+      const int jn = j + (pair ? 2 : 1);
+      if (jn < je) request(jn);
+      __builtin_amdgcn_sched_barrier(0);
+      read_out(X, weight(j, (istar >= 0 && j > istar) ? j - 1 : j));
+      if (pair) {
+        float4 Y[ST::NV];
+        if (j + 1 == m - 1) {
+          reopen(Y);
+        } else {
+          const TS* src = states + (size_t)sP[j + 1] * D;
+#pragma unroll
+          for (int r = 0; r < ST::NV; ++r) Y[r] = ld_group<true>(src, tid + 256 * r);
+        }
+        read_out(Y, weight(j + 1, j));
+        merge(j, X, Y);
+      }
+      j = jn;
+    }
+    if (j < j1) {  // the newest state
+      float4 X[ST::NV];
+      reopen(X);
+      read_out(X, weight(j, (istar >= 0 && j > istar) ? j - 1 : j));
+      if (SB && b) close(j, X);
+    }
+  } else {
+    for (int j = j0; j < j1; ++j) {
+      const bool is_open = (j == m - 1);
+      float4 X[ST::NV];
+      if (is_open) {
+#pragma unroll
+        for (int r = 0; r < ST::NV; ++r) X[r] = Sopen[r];
       } else {
-        const TS* src = states + (size_t)sP[j2] * D;
+        const TS* src = states + (size_t)sP[j] * D;
 #pragma unroll
-        for (int r = 0; r < ST::NV; ++r) Y[r] = ld_group<true>(src, tid + 256 * r);
+        for (int r = 0; r < ST::NV; ++r) X[r] = ld_group<true>(src, tid + 256 * r);
       }
-      const float e2 = __expf((float)(Gn - sF[j2]));
-      const float w2 = a.skip_readout ? 0.f : sLam[j] * e2;
-      const float e1 = __expf((float)(Gn - sF[j]));
-      float z0 = 0.f, z1 = 0.f, z2 = 0.f, z3 = 0.f;
-      TS* dst = states + (size_t)sP[j] * D;
+      read_out(X, weight(j, (istar >= 0 && j > istar) ? j - 1 : j));
+      if (j == istar) {
+        float4 Y[ST::NV];
+        if (j + 1 == m - 1) {
 #pragma unroll
-      for (int r = 0; r < ST::NV; ++r) {
-        z0 += qr[r] * Y[r].x;
-        z1 += qr[r] * Y[r].y;
-        z2 += qr[r] * Y[r].z;
-        z3 += qr[r] * Y[r].w;
-        float4 s;
-        s.x = e1 * X[r].x + e2 * Y[r].x;
-        s.y = e1 * X[r].y + e2 * Y[r].y;
-        s.z = e1 * X[r].z + e2 * Y[r].z;
-        s.w = e1 * X[r].w + e2 * Y[r].w;
-        st_group(dst, tid + 256 * r, s);
+          for (int r = 0; r < ST::NV; ++r) Y[r] = Sopen[r];
+        } else {
+          const TS* src = states + (size_t)sP[j + 1] * D;
+#pragma unroll
+          for (int r = 0; r < ST::NV; ++r) Y[r] = ld_group<true>(src, tid + 256 * r);
+        }
+        read_out(Y, weight(j + 1, j));
+        merge(j, X, Y);
+        ++j;  // the pair is done
+      } else if (SB && is_open && b) {
+        close(j, X);
       }
-      o4[0] += w2 * z0;
-      o4[1] += w2 * z1;
-      o4[2] += w2 * z2;
-      o4[3] += w2 * z3;
-      ++j;  // the pair is done
-    } else if (SB && is_open && b) {
-      // the newest state closes: its bfloat16 copy goes to its slot, in its
-      // own frame (a merge with its left neighbour is handled above)
-      TS* dst = states + (size_t)sP[j] * D;
-#pragma unroll
-      for (int r = 0; r < ST::NV; ++r) st_group(dst, tid + 256 * r, X[r]);
     }
   }
 
@@ -582,14 +661,32 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(DecodeArgs a) {
                                 [&](int r) { return ld_group<true>(newest, threadIdx.x + 256 * r); });
 }
 
-// Workgroups per head: enough for about four per compute unit over all heads,
-// at most kMaxSplit, and at least two states per workgroup.
-int decode_splits(int nheads, int C) {
-  int ns = (1024 + nheads - 1) / nheads;
-  ns = ns < kMaxSplit ? ns : kMaxSplit;
-  const int byc = C / 2 > 1 ? C / 2 : 1;
-  ns = ns < byc ? ns : byc;
-  return ns > 1 ? ns : 1;
+// Workgroups per head.  With the next state always in flight one workgroup per
+// compute unit keeps memory busy (two where a state has less than 8192
+// elements), and a second one only repeats the decisions: 32 heads of 128
+// float32 states, 128 x 128, take 56.6 / 58.2 us a step split by 5 / 8 (at most
+// 256 workgroups), 74.3 / 64.5 us by 9 / 16.  So the split is the one whose
+// rounds over the chip, each a workgroup's states and its decisions (worth
+// about 15 states), are shortest; at most kMaxSplit, and at least two states
+// per workgroup.  Heads beyond the chip: 384 of 30 states, 128 x 64, 73.7 us
+// unsplit, 75.7 / 80.1 by 2 / 3; 384 of 128 bfloat16 states 160 us unsplit, 147
+// by 2; 640 of 100 states, 128 x 128, 711 us unsplit, 636 by 2.  From four
+// rounds on the rounds' rest no longer counts and the unsplit step, without a
+// second kernel, is taken.
+int decode_splits(int nheads, int C, int D) {
+  constexpr int kDecide = 15;
+  if (nheads >= 1024) return 1;
+  const int slots = D >= 8192 ? 256 : 512;
+  const int most = C / 2 < kMaxSplit ? C / 2 : kMaxSplit;
+  int best = 1, cost = 0;
+  for (int ns = 1; ns <= most; ++ns) {
+    const int c = (nheads * ns + slots - 1) / slots * (kDecide + (C + ns - 1) / ns);
+    if (ns == 1 || c < cost) {
+      cost = c;
+      best = ns;
+    }
+  }
+  return best;
 }
 
 template <int DK, int DV, typename Tin, typename Tout, typename TS>
