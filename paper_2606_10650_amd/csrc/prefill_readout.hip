@@ -110,7 +110,12 @@ __device__ __forceinline__ int tile_of(int wv, int nt) {
   return (nt & 1) ? base + 2 * RWAVE - 1 - wv : base + wv;
 }
 
-template <int DK, int DV, typename Tin, typename Tout>
+// PARTS: workgroups that share the token tiles of one (head, chunk, 32 value
+// columns).  The two waves of a SIMD take turns at its matrix core, so where
+// the grid leaves compute units idle the halves of a workgroup's waves serve
+// their tiles in two workgroups: every loop over the states runs with one
+// wave's chains per SIMD.
+template <int DK, int DV, typename Tin, typename Tout, int PARTS>
 __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, PrefillWS w,
                                                                SegPlan plan, int seg, int lw) {
   if (!cache_matches(a.cache, a.desc)) return;  // refused call (see the prep kernel)
@@ -126,12 +131,14 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
   int cs, ce;
   seg_range(plan, seg, &cs, &ce);
   const int nchs = ce - cs;
-  // id -> (XCD x, i); i -> (head group, chunk, column group), column group fastest
+  // id -> (XCD x, i); i -> (head group, chunk, part, column group), column group
+  // fastest; part: which RWAVE / PARTS waves' tiles the workgroup serves
   const int bid = blockIdx.x;
   const int i = bid >> 3;
   const int cg = i % NCG;
-  const int c = cs + (i / NCG) % nchs;
-  const int h = (i / (NCG * nchs)) * 8 + (bid & 7);
+  const int part = i / NCG % PARTS;
+  const int c = cs + (i / (NCG * PARTS)) % nchs;
+  const int h = (i / (NCG * PARTS * nchs)) * 8 + (bid & 7);
   if (h >= nh) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -176,6 +183,12 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
   const int nrow = min(RL, T - c0);
   const int nblk = (nrow + 31) >> 5;
 
+  // whether the wave serves its tiles (their first is the earliest) here; else it
+  // only helps to load.  (With one part every wave takes the same path: a
+  // branch around its chains cost the 16k-token prompts 1.6%.)
+  const bool act = PARTS == 1 || __builtin_amdgcn_readfirstlane(
+                                     wv * PARTS / RWAVE == part && 32 * tile_of<NT>(wv, 0) < nrow);
+
   // ------------------------------------------------ set-up: every load first
   const char* lst = list_at(w, h, c, plan.nch);
   const ListEntry* ent = reinterpret_cast<const ListEntry*>(lst + 16);
@@ -219,7 +232,7 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     tr[nt] = 32 * tile_of<NT>(wv, nt) + l32;
-    rv[nt] = tr[nt] < nrow;
+    rv[nt] = act && tr[nt] < nrow;
     acc[nt] = zero16();
     const Tin* qrow = Qin + (size_t)(c0 + (rv[nt] ? tr[nt] : 0)) * DK;
 #pragma unroll
@@ -520,7 +533,7 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
     // the LDS counter only), so each wave waits for its own requests first.
     __builtin_amdgcn_s_waitcnt(VM_DRAIN);
     __syncthreads();
-    if constexpr (P::PREF) opload(reinterpret_cast<const Tin*>(ring), saX);
+    if (P::PREF && act) opload(reinterpret_cast<const Tin*>(ring), saX);
     for (int J = 0; 2 * J < m; ++J) {
       if (J > 0) {
         __builtin_amdgcn_s_waitcnt(WAIT);
@@ -534,13 +547,18 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
       // (the object numbers are read here, so that the requests below need not
       // wait for an LDS read behind the operand reads)
       const int ob0 = obj_of(2 * (J + LEAD)), ob1 = obj_of(2 * (J + LEAD) + 1);
-      sub(2 * J, saX, A0, A0 + P::SLICE, saY, [&]() __attribute__((always_inline)) {
+      auto requests = [&]() __attribute__((always_inline)) {
         lam_dma(jl, dt0);
         lam_dma(jl + 1, dt1);
         dma2((J + LEAD) % P::NPAIR, ob0, ob1);
-      });
-      __builtin_amdgcn_sched_barrier(0);
-      sub(2 * J + 1, saY, A0 + P::SLICE, A2, saX, nothing);
+      };
+      if (act) {
+        sub(2 * J, saX, A0, A0 + P::SLICE, saY, requests);
+        __builtin_amdgcn_sched_barrier(0);
+        sub(2 * J + 1, saY, A0 + P::SLICE, A2, saX, nothing);
+      } else {
+        requests();
+      }
     }
     if constexpr (NT > 1) {
 #pragma unroll
@@ -711,10 +729,10 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     const int t0 = tile_of<NT>(wv, 0);
-    const bool a0 = sb <= t0 && 32 * t0 < nrow;
+    const bool a0 = act && sb <= t0 && 32 * t0 < nrow;
     if constexpr (NT == 2) {
       const int t1 = tile_of<NT>(wv, 1);
-      const bool a1 = sb <= t1 && 32 * t1 < nrow;
+      const bool a1 = act && sb <= t1 && 32 * t1 < nrow;
       if (a0 && a1)
         blockT(I0{}, I2{}, sb);
       else if (a1)
@@ -768,20 +786,29 @@ static hipError_t launch_readout_t(const PrefillArgs& a, const SegPlan& p, int s
   int cs, ce;
   seg_range(p, seg, &cs, &ce);
   const int nchs = ce - cs;
-  const long long grid = (long long)round_up(nh, 8) * nchs * (DV / NC);
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  const long long grid1 = (long long)round_up(nh, 8) * nchs * (DV / NC);
+  if (grid1 > 0x7fffffffLL) return hipErrorInvalidValue;
   const int lw = readout_window<DK, Tin>(a.desc.C);
   if (lw < 0) return hipErrorInvalidValue;
   const size_t shm = RO<DK, Tin>::smem_bytes(a.desc.C, lw);
-  auto launch = [&](auto k) -> hipError_t {
+  auto launch = [&](auto k, int parts) -> hipError_t {
     if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
         hipSuccess)
       return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(RTHR), shm, s, a, w, p, seg, lw);
+    hipLaunchKernelGGL(k, dim3((unsigned)(grid1 * parts)), dim3(RTHR), shm, s, a, w, p, seg, lw);
     return hipGetLastError();
   };
-  if (a.out_dtype == DLA_F32) return launch(prefill_readout_kernel<DK, DV, Tin, float>);
-  return launch(prefill_readout_kernel<DK, DV, Tin, bf16_t>);
+  // Two parts where both fit on the chip at once, beside the scan of the next
+  // segments (one workgroup per compute unit each): a second round would cost
+  // what the halves save.  15 float32 heads of 64 x 64, 1531 tokens in two
+  // calls and a decode step: 616 -> 526 us.
+  const bool scanning = seg + 1 < p.nseg && pipelined(a.T, a.in_dtype, true, a.serial != 0);
+  const bool two = 2 * grid1 + (scanning ? nh : 0) <= 256;
+  if (a.out_dtype == DLA_F32)
+    return two ? launch(prefill_readout_kernel<DK, DV, Tin, float, 2>, 2)
+               : launch(prefill_readout_kernel<DK, DV, Tin, float, 1>, 1);
+  return two ? launch(prefill_readout_kernel<DK, DV, Tin, bf16_t, 2>, 2)
+             : launch(prefill_readout_kernel<DK, DV, Tin, bf16_t, 1>, 1);
 }
 
 template <int DK, int DV>
