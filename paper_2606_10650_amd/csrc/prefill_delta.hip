@@ -81,7 +81,8 @@ struct DeltaP {
     size_t off = K_BYTES + V_BYTES + T_BYTES;
     off += 3 * MAT;                       // sM (then sR), sVV, sW
     off += 2 * (size_t)SWAVE * SL * 4;    // sPc, sPq
-    off += (size_t)SL * 4 * 9;            // float rows, boundary overrides
+    off += (size_t)SL * 8;                // sG
+    off += (size_t)SL * 4 * 8;            // float rows, boundary overrides
     off += 64 + 128;                      // sRed, sMisc
     if (C > kMaxRegC) off += (size_t)C * (8 + 4 + 4);
     return round_up(off, 16);
@@ -104,6 +105,25 @@ __device__ __forceinline__ bool piece_bad(const u32x4& v, float) {
 }
 __device__ __forceinline__ bool is_bad(float x) {
   return (__float_as_uint(x) & 0x7F800000u) == 0x7F800000u;
+}
+
+// exp(x) for a sum of gates x <= 0: n ln 2 taken off, a Taylor polynomial of
+// degree 9 on |r| <= ln 2 / 2 (remainder r^10 / 10! < 1e-11), scaled by 2^n.
+__device__ __forceinline__ double exp_gate(double x) {
+  x = x > -800.0 ? x : -800.0;  // (0 in float64)
+  const double n = __builtin_rint(x * 1.4426950408889634);
+  const double r = __builtin_fma(n, -0.6931471805599453, x);
+  double p = 1.0 / 362880.0;
+  p = __builtin_fma(p, r, 1.0 / 40320.0);
+  p = __builtin_fma(p, r, 1.0 / 5040.0);
+  p = __builtin_fma(p, r, 1.0 / 720.0);
+  p = __builtin_fma(p, r, 1.0 / 120.0);
+  p = __builtin_fma(p, r, 1.0 / 24.0);
+  p = __builtin_fma(p, r, 1.0 / 6.0);
+  p = __builtin_fma(p, r, 0.5);
+  p = __builtin_fma(p, r, 1.0);
+  p = __builtin_fma(p, r, 1.0);
+  return __builtin_ldexp(p, (int)n);
 }
 
 // NR: see the gated scan.
@@ -156,8 +176,8 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
   float* sW = sVV + SL * MRS;
   float* sPc = sW + SL * MRS;     // [SWAVE][SL] the waves' shares of y . v
   float* sPq = sPc + SWAVE * SL;  //                              |y|^2
-  float* sGc = sPq + SWAVE * SL;  // G_t - G(chunk start)
-  float* sA = sGc + SL;           // exp(sGc[t])
+  double* sG = reinterpret_cast<double*>(sPq + SWAVE * SL);  // G_t - G(chunk start)
+  float* sA = reinterpret_cast<float*>(sG + SL);             // exp(sG[t])
   float* sAl = sA + SL;           // alpha_t
   float* sAl2 = sAl + SL;         // alpha_t^2
   float* sDe = sAl2 + SL;         // exp(G_end - G_t)
@@ -244,6 +264,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
   const Tin* Kin = static_cast<const Tin*>(a.k) + tok0 * DK;
   const Tin* Vin = static_cast<const Tin*>(a.v) + tok0 * DV;
   const double* Gtok = w.Gtok + tok0;
+  const float* gate = a.g + tok0;
   const float* bt = beta + tok0;
   int32_t* death = w.death + tok0;
   float* Uh = U + tok0 * DV;
@@ -251,7 +272,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
   // next chunk's tokens in registers (see the gated scan)
   u32x4 pk[K16], pv[V16];
   double gpre = 0.0;
-  float bepre = 0.f;
+  float fpre = 0.f, bepre = 0.f;
   int bpre = -1, mpre = -1;
   auto prefetch = [&](int c0n) __attribute__((always_inline)) {
     const int nr = min(SL, T - c0n);
@@ -268,6 +289,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     if (tid < SL) {
       const int t = min(tid, nr - 1);
       gpre = Gtok[c0n + t];
+      fpre = gate[c0n + t];
       bepre = bt[c0n + t];
       bpre = (a.b_ovr && tid < nr) ? a.b_ovr[tok0 + c0n + tid] : (int8_t)-1;
       mpre = (a.m_ovr && tid < nr) ? a.m_ovr[tok0 + c0n + tid] : -1;
@@ -312,18 +334,20 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     if (tid < SL) {
       const int t = tid;
       const double Glast = __shfl(gpre, nrow - 1, 64);
-      const float gc = (float)(gpre - Gprev);
-      const float gcp = __shfl_up(gc, 1, 64);  // token t - 1 (t >= 1)
-      const float gt = t == 0 ? gc : gc - gcp;
+      // Decays across tokens come from float64 differences of G, a token's own
+      // from its gate: after a steep gate (a reset), float32 offsets from the
+      // chunk start would round the later tokens' decays to that gate's ulp.
+      const double gd = gpre - Gprev;
       const float be = t < nrow ? bepre : 0.f;
-      sGc[t] = gc;
-      sA[t] = __expf(gc);
-      sAl[t] = (t < nrow) ? __expf(gt) : 0.f;
-      sAl2[t] = (t < nrow) ? __expf(2.f * gt) : 0.f;
-      sDe[t] = (t < nrow) ? __expf((float)(Glast - gpre)) : 0.f;
+      sG[t] = gd;
+      sA[t] = (float)exp_gate(gd);
+      sAl[t] = (t < nrow) ? __expf(fpre) : 0.f;
+      sAl2[t] = (t < nrow) ? __expf(2.f * fpre) : 0.f;
+      sDe[t] = (t < nrow) ? (float)exp_gate(Glast - gpre) : 0.f;
       sBeta[t] = be;
       sBo[t] = bpre;
-      bad |= is_bad(gc) || is_bad(be);
+      // (a positive gate expands the state: token by token too)
+      bad |= !(fpre <= 0.f) || is_bad((float)gd) || is_bad(be);
       if (t == 0) sGlast[0] = Glast;
     }
     sPq[wv * SL + lane] = kpart;
@@ -390,14 +414,14 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
             mma16(g, Frag<Tin>::load(pa + 32 * ks), Frag<Tin>::load(pb + 32 * ks));
         }
         const int s = 16 * tc + c16;
-        const float gs = sGc[s];
+        const double gs = sG[s];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int t = 16 * tr + 4 * q4 + r;
           if (isv)
             sVV[t * MRS + s] = g[r];
           else
-            sM[t * MRS + s] = s < t ? __expf(sGc[t] - gs) * g[r] : 0.f;
+            sM[t * MRS + s] = s < t ? (float)exp_gate(sG[t] - gs) * g[r] : 0.f;
           if (s == t) (isv ? sV2 : sKK)[t] = g[r];
         }
       }
