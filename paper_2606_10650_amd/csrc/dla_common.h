@@ -193,6 +193,22 @@ __device__ __forceinline__ void wave_scan_affine(float& A, float& B) {
   affine_step<0x143, 0xC>(A, B);
 }
 
+template <int CTRL, int RMASK>
+__device__ __forceinline__ void affine_step(double& A, double& B) {
+  const double Ao = dpp_d<CTRL, RMASK>(1.0, A);
+  const double Bo = dpp_d<CTRL, RMASK>(0.0, B);
+  B = __builtin_fma(A, Bo, B);
+  A = A * Ao;
+}
+__device__ __forceinline__ void wave_scan_affine(double& A, double& B) {
+  affine_step<0x111, 0xF>(A, B);
+  affine_step<0x112, 0xF>(A, B);
+  affine_step<0x114, 0xF>(A, B);
+  affine_step<0x118, 0xF>(A, B);
+  affine_step<0x142, 0xA>(A, B);
+  affine_step<0x143, 0xC>(A, B);
+}
+
 // Sum of a float over the wavefront through DPP row shifts and broadcasts
 // (every lane gets it).
 __device__ __forceinline__ float wave_total_dpp(float x) {
@@ -205,18 +221,21 @@ __device__ __forceinline__ float wave_total_dpp(float x) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
-// Sum of a double over the wavefront (every lane gets it).
+// Sums of a double over the wavefront.
 template <int CTRL, int RMASK>
 __device__ __forceinline__ void sum_step_d(double& x) {
   x += dpp_d<CTRL, RMASK>(0.0, x);
 }
-__device__ __forceinline__ double wave_sum_d(double x) {
+__device__ __forceinline__ void wave_prefix_d(double& x) {  // inclusive, over the lanes
   sum_step_d<0x111, 0xF>(x);
   sum_step_d<0x112, 0xF>(x);
   sum_step_d<0x114, 0xF>(x);
   sum_step_d<0x118, 0xF>(x);
   sum_step_d<0x142, 0xA>(x);
   sum_step_d<0x143, 0xC>(x);
+}
+__device__ __forceinline__ double wave_sum_d(double x) {
+  wave_prefix_d(x);
   return readlane_d(x, 63);
 }
 

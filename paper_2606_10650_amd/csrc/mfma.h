@@ -86,10 +86,37 @@ __device__ __forceinline__ void mma16(f32x4& acc, const f32x8& a, const f32x8& b
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
 }
-// the K = 16 product of float32 operands, 4 k-values per lane
-__device__ __forceinline__ void mma16(f32x4& acc, const f32x4& a, const f32x4& b) {
+// float64 16 x 16 tiles, K = 16 per call: step r takes the k set 4 r + l / 16, and
+// lane l holds row (A) or column (B) l % 16; output: column l % 16 and rows 4 r + l
+// / 16, so that a result serves as the next product's B operand.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void mma16(f64x4& acc, const f64x4& a, const f64x4& b) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
+  for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b[r], acc, 0, 0, 0);
+}
+// The tile's K = 32 product of the inputs, summed in float64: bfloat16 operands by
+// bfloat16 MFMAs over 16 products each (exact products, one float32 sum), which
+// takes half the time of float64 MFMAs; float32 operands by float64 MFMAs.
+// gram_row: the output row of element r.
+__device__ __forceinline__ void gram16(f64x4& acc, const bf16x8& a, const bf16x8& b) {
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const s16x8 x = __builtin_bit_cast(s16x8, a), y = __builtin_bit_cast(s16x8, b);
+  f32x4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
+  z0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 0, 1, 2, 3),
+                                                 __builtin_shufflevector(y, y, 0, 1, 2, 3), z0, 0, 0, 0);
+  z1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(x, x, 4, 5, 6, 7),
+                                                 __builtin_shufflevector(y, y, 4, 5, 6, 7), z1, 0, 0, 0);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc[r] += (double)z0[r] + (double)z1[r];
+}
+__device__ __forceinline__ void gram16(f64x4& acc, const f32x8& a, const f32x8& b) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[e], (double)b[e], acc, 0, 0, 0);
+}
+template <typename Tin>
+__device__ __forceinline__ int gram_row(int r, int q4) {
+  return sizeof(Tin) == 2 ? 4 * q4 + r : 4 * r + q4;
 }
 
 // A float32 operand as three bfloat16 terms, largest first, whose sum is its

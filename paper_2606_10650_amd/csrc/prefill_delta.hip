@@ -22,12 +22,19 @@
 // for the state S_0 before the chunk, and the same sum over r >= p with S_0 = 0
 // for a state that begins at token p of the chunk.  So a chunk costs the Gram
 // products, one triangular solve for W (16 x 16 diagonal blocks by
-// substitution, the blocks below by float32 MFMAs) and the products for y; the
+// substitution, the blocks below by MFMAs) and the products for y; the
 // scores need y . v and |y|^2, explicit for S_0 and, once a boundary falls in
 // the chunk, from tables over the starts p (suffix sums of W beta (.) V V^T and
 // of its quadratic form).  The decisions are the gated scan's (scan_decide.h).
 // Products that carry float32 values run as bfloat16 MFMAs over three-term
 // splits (16-bit inputs) or as float32 MFMAs.
+//
+// The 64 x 64 part (Gram sums, decays, the solve, the sums over starts and the
+// recurrence of |S|^2) is float64: the solve amplifies the rounding of M where
+// keys repeat, and |S|^2 is a sum of terms of both signs.  In float32 the scores
+// were off by up to 2e-6 where a float32 token by token scan is off by 5e-7
+// (beta near 2: 4e-6, the states 3e-6), now by 4e-7 and the states by 2e-7
+// (5e-7, 6e-7); 8 x 16 heads x 4k tokens took 2.96 ms, now 3.30.
 //
 // Bound: latency, as the gated scan: a chain of eight phases between barriers,
 // about 20 us a chunk at d = 128 (128 heads x 4096 tokens: 1.3 ms).  Taking the
@@ -65,24 +72,25 @@ struct DeltaP {
   static constexpr int VRS = DV + EPP;  // sV [SL][VRS]
   static constexpr int TRS = SL + EPP;  // sKt [DK][TRS], sVt [DV][TRS] (transposed, 16-bit inputs)
   static constexpr bool TRANS = E == 2;
-  static constexpr int MRS = SL + 4;    // sM, sVV, sW [SL][MRS], 16-byte aligned rows
   static constexpr int RRS = SL + 1;    // sR, sQ [SL][RRS]
+  // sM, sVV, sW: float64, the 10 16 x 16 tiles on and below the diagonal
+  static constexpr int MRS = 16 + 1;    // row stride of a tile
+  static constexpr int MTS = 16 * MRS;  // tile
+  static constexpr size_t MAT = 10 * (size_t)MTS * 8;
   static constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
-  static constexpr size_t MAT = (size_t)SL * MRS * 4;
-  // sK, with 16-bit inputs dead once the Gram products and the carry are formed:
-  // then the row tables take its bytes (float32 inputs read it in the state
-  // advance)
-  static constexpr size_t K_BYTES = cmax((size_t)SL * KRS * E, TRANS ? RowTables::BYTES : 0);
-  // sV, dead at the same time; then sQ
-  static constexpr size_t V_BYTES = cmax((size_t)SL * VRS * E, MAT);
-  static constexpr size_t T_BYTES = TRANS ? (size_t)(DK + DV) * TRS * E : RowTables::BYTES;
-  static_assert(K_BYTES % 16 == 0 && V_BYTES % 16 == 0 && T_BYTES % 16 == 0, "alignment");
+  static constexpr size_t K_BYTES = (size_t)SL * KRS * E;
+  // sV, dead once the Gram products and the carry are formed; then sQ
+  static constexpr size_t V_BYTES = cmax((size_t)SL * VRS * E, (size_t)SL * RRS * 4);
+  static constexpr size_t T_BYTES = TRANS ? (size_t)(DK + DV) * TRS * E : 0;
+  static_assert(MAT >= (size_t)SL * RRS * 4 && MAT >= RowTables::BYTES, "aliases of sM and sVV");
+  static_assert(K_BYTES % 16 == 0 && V_BYTES % 16 == 0 && T_BYTES % 16 == 0 && MAT % 16 == 0,
+                "alignment");
   static size_t smem_bytes(int C) {
     size_t off = K_BYTES + V_BYTES + T_BYTES;
-    off += 3 * MAT;                       // sM (then sR), sVV, sW
+    off += 3 * MAT;                       // sM (then sR), sVV (then the row tables), sW
     off += 2 * (size_t)SWAVE * SL * 4;    // sPc, sPq
-    off += (size_t)SL * 8;                // sG
-    off += (size_t)SL * 4 * 8;            // float rows, boundary overrides
+    off += (size_t)SL * 8 * 4;            // sG, sAl2, sKK, sV2
+    off += (size_t)SL * 4 * 5;            // float rows, boundary overrides
     off += 64 + 128;                      // sRed, sMisc
     if (C > kMaxRegC) off += (size_t)C * (8 + 4 + 4);
     return round_up(off, 16);
@@ -140,7 +148,8 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
   using XT = typename std::conditional<P::E == 2, Split3, f32x8>::type;
   constexpr int D = DK * DV;
   constexpr int NI = P::NI, NW = P::NW;
-  constexpr int KRS = P::KRS, VRS = P::VRS, TRS = P::TRS, MRS = P::MRS, RRS = P::RRS;
+  constexpr int KRS = P::KRS, VRS = P::VRS, TRS = P::TRS, RRS = P::RRS;
+  constexpr int MRS = P::MRS, MTS = P::MTS;
   constexpr int K16 = P::K16, V16 = P::V16;
   const int h = blockIdx.x;
   int tid = threadIdx.x;
@@ -169,24 +178,24 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
   float* sQ = reinterpret_cast<float*>(smem + P::K_BYTES);                // (alias of sV)
   Tin* sKt = reinterpret_cast<Tin*>(smem + P::K_BYTES + P::V_BYTES);
   Tin* sVt = sKt + DK * TRS;
-  const RowTables rows(P::TRANS ? smem : smem + P::K_BYTES + P::V_BYTES);
-  float* sM = reinterpret_cast<float*>(smem + P::K_BYTES + P::V_BYTES + P::T_BYTES);
-  float* sR = sM;                 // R[p][t] at [t RRS + p] (once M is no longer read)
-  float* sVV = sM + SL * MRS;
-  float* sW = sVV + SL * MRS;
-  float* sPc = sW + SL * MRS;     // [SWAVE][SL] the waves' shares of y . v
+  double* sM = reinterpret_cast<double*>(smem + P::K_BYTES + P::V_BYTES + P::T_BYTES);
+  float* sR = reinterpret_cast<float*>(sM);  // R[p][t] at [t RRS + p] (once M is no longer read)
+  double* sVV = sM + 10 * MTS;
+  const RowTables rows(reinterpret_cast<char*>(sVV));  // (once the tables for R and Q are built)
+  double* sW = sVV + 10 * MTS;
+  double* sG = sW + 10 * MTS;     // G_t - G(chunk start)
+  double* sAl2 = sG + SL;         // alpha_t^2
+  double* sKK = sAl2 + SL;        // |k_t|^2
+  double* sV2 = sKK + SL;         // |v_t|^2
+  double* sRed = sV2 + SL;        // [8] the waves' shares of |S|^2
+  float* sPc = reinterpret_cast<float*>(sRed + 8);  // [SWAVE][SL] the waves' shares of y . v
   float* sPq = sPc + SWAVE * SL;  //                              |y|^2
-  double* sG = reinterpret_cast<double*>(sPq + SWAVE * SL);  // G_t - G(chunk start)
-  float* sA = reinterpret_cast<float*>(sG + SL);             // exp(sG[t])
+  float* sA = sPq + SWAVE * SL;   // exp(sG[t])
   float* sAl = sA + SL;           // alpha_t
-  float* sAl2 = sAl + SL;         // alpha_t^2
-  float* sDe = sAl2 + SL;         // exp(G_end - G_t)
+  float* sDe = sAl + SL;          // exp(G_end - G_t)
   float* sBeta = sDe + SL;        // beta_t (0 past the chunk's end)
-  float* sKK = sBeta + SL;        // |k_t|^2
-  float* sV2 = sKK + SL;          // |v_t|^2
-  int32_t* sBo = reinterpret_cast<int32_t*>(sV2 + SL);  // boundary overrides
-  float* sRed = reinterpret_cast<float*>(sBo + SL);     // [16]
-  int32_t* sMisc = reinterpret_cast<int32_t*>(sRed + 16);
+  int32_t* sBo = reinterpret_cast<int32_t*>(sBeta + SL);  // boundary overrides
+  int32_t* sMisc = sBo + SL;
   // sMisc: 0, 1 boundary mask; 2 start of the rows left (-1: none); 3 go on with
   // the row tables; 4, 5 non-finite inputs of an even, an odd chunk; 6 the
   // decision of the token by token path
@@ -248,17 +257,17 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
 #pragma unroll
       for (int r = 0; r < 4; ++r) x += S[i][r] * S[i][r];
     x = wave_total_dpp(x);
-    if (lane == 0) sRed[wv] = x;
+    if (lane == 0) sRed[wv] = (double)x;
   };
-  auto norm2 = [&]() __attribute__((always_inline)) -> float {
-    float b = 0.f;
+  auto norm2 = [&]() __attribute__((always_inline)) -> double {
+    double b = 0.0;
 #pragma unroll
     for (int i = 0; i < NW; ++i) b += sRed[i];
     return b;
   };
   norm_share();
-  // W's blocks above the diagonal stay zero
-  for (int i = tid; i < SL * MRS; i += STHR) sW[i] = 0.f;
+  // the first row of W's diagonal blocks stays zero
+  for (int i = tid; i < 10 * MTS; i += STHR) sW[i] = 0.0;
   if (tid < 2) sMisc[4 + tid] = 0;
 
   const Tin* Kin = static_cast<const Tin*>(a.k) + tok0 * DK;
@@ -342,7 +351,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
       sG[t] = gd;
       sA[t] = (float)exp_gate(gd);
       sAl[t] = (t < nrow) ? __expf(fpre) : 0.f;
-      sAl2[t] = (t < nrow) ? __expf(2.f * fpre) : 0.f;
+      sAl2[t] = (t < nrow) ? exp_gate(2.0 * (double)fpre) : 0.0;
       sDe[t] = (t < nrow) ? (float)exp_gate(Glast - gpre) : 0.f;
       sBeta[t] = be;
       sBo[t] = bpre;
@@ -354,7 +363,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     if (__ballot(bad) && lane == 0) *sBad = 1;
     __syncthreads();
     const double Gnext = sGlast[0];  // G after the chunk's last token
-    const float b0 = norm2();        // |S|^2
+    const double b0 = norm2();       // |S|^2
     // Token by token when an input of the chunk or the state is not finite, or
     // when a token's step is not a contraction (beta |k|^2 outside [0, 2]): the
     // tables range over starts that the boundaries may exclude, and only
@@ -364,7 +373,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     for (int i = 0; i < SWAVE; ++i) kk += sPq[i * SL + lane];
     const float bk = sBeta[lane] * kk;
     const bool serial =  // (workgroup-uniform)
-        *sBad != 0 || is_bad(b0) || __ballot(!(bk >= 0.f && bk <= 2.f)) != 0;
+        *sBad != 0 || is_bad((float)b0) || __ballot(!(bk >= 0.f && bk <= 2.f)) != 0;
     if (tid == 0) sMisc[4 + (((c0 / SL) & 1) ^ 1)] = 0;
     const int mforce = mpre;  // merge override of the lane's token (wave 0)
     fresh_lane();
@@ -399,29 +408,30 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         const int x = isv ? ti - 10 : ti;
         const int tr = x < 1 ? 0 : (x < 3 ? 1 : (x < 6 ? 2 : 3));
         const int tc = x - tr * (tr + 1) / 2;
-        f32x4 g = {0.f, 0.f, 0.f, 0.f};
+        f64x4 g = {0.0, 0.0, 0.0, 0.0};
         if (!isv) {
           const Tin* pa = sK + (16 * tr + c16) * KRS + 8 * q4;
           const Tin* pb = sK + (16 * tc + c16) * KRS + 8 * q4;
 #pragma unroll
           for (int ks = 0; ks < DK / 32; ++ks)
-            mma16(g, Frag<Tin>::load(pa + 32 * ks), Frag<Tin>::load(pb + 32 * ks));
+            gram16(g, Frag<Tin>::load(pa + 32 * ks), Frag<Tin>::load(pb + 32 * ks));
         } else {
           const Tin* pa = sV + (16 * tr + c16) * VRS + 8 * q4;
           const Tin* pb = sV + (16 * tc + c16) * VRS + 8 * q4;
 #pragma unroll
           for (int ks = 0; ks < DV / 32; ++ks)
-            mma16(g, Frag<Tin>::load(pa + 32 * ks), Frag<Tin>::load(pb + 32 * ks));
+            gram16(g, Frag<Tin>::load(pa + 32 * ks), Frag<Tin>::load(pb + 32 * ks));
         }
         const int s = 16 * tc + c16;
         const double gs = sG[s];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int t = 16 * tr + 4 * q4 + r;
+          const int row = gram_row<Tin>(r, q4), t = 16 * tr + row;
+          const int at = x * MTS + row * MRS + c16;
           if (isv)
-            sVV[t * MRS + s] = g[r];
+            sVV[at] = g[r];
           else
-            sM[t * MRS + s] = s < t ? (float)exp_gate(sG[t] - gs) * g[r] : 0.f;
+            sM[at] = s < t ? exp_gate(sG[t] - gs) * g[r] : 0.0;
           if (s == t) (isv ? sV2 : sKK)[t] = g[r];
         }
       }
@@ -437,10 +447,12 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           for (int i = 0; i < 4; ++i) {
             const Tin* kr = sK + (16 * i + c16) * KRS + 32 * kk + 4 * q4;
             const FT ka = load_4x2<Tin>(kr, kr + 16);
+            f32x4 z = {0.f, 0.f, 0.f, 0.f};  // (short sums, added at the end)
             if constexpr (P::E == 2)
-              mma16_split(X[i], ka, sb);
+              mma16_split(z, ka, sb);
             else
-              mma16(X[i], ka, sb);
+              mma16(z, ka, sb);
+            X[i] += z;
           }
         }
 #pragma unroll
@@ -464,56 +476,54 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
       // W[t][r] = M[t][r] - sum_{r<s<t} M[t][s] beta_s W[s][r]: within the 16 x 16
       // diagonal blocks by substitution (wave 0, lane = block and column r) ...
       if (wv == 0) {
-        const float* Mb = sM + 16 * q4 * MRS + 16 * q4;
-        float bw[16];  // beta_s W[s][r]
+        const double* Mb = sM + q4 * (q4 + 3) / 2 * MTS;
+        double* Wb = sW + q4 * (q4 + 3) / 2 * MTS;
+        double bw[16];  // beta_s W[s][r]
         float be[16];
 #pragma unroll
         for (int s4 = 0; s4 < 4; ++s4) {
           const float4 b = *reinterpret_cast<const float4*>(sBeta + 16 * q4 + 4 * s4);
           be[4 * s4] = b.x; be[4 * s4 + 1] = b.y; be[4 * s4 + 2] = b.z; be[4 * s4 + 3] = b.w;
         }
-        bw[0] = 0.f;
+        bw[0] = 0.0;
 #pragma unroll
         for (int t = 1; t < 16; ++t) {
-          float mrow[16];
+          double x0 = Mb[t * MRS + c16], x1 = 0.0;
 #pragma unroll
-          for (int s4 = 0; 4 * s4 < t; ++s4) {
-            const float4 x = *reinterpret_cast<const float4*>(Mb + t * MRS + 4 * s4);
-            mrow[4 * s4] = x.x; mrow[4 * s4 + 1] = x.y; mrow[4 * s4 + 2] = x.z; mrow[4 * s4 + 3] = x.w;
-          }
-          float x0 = Mb[t * MRS + c16], x1 = 0.f;
-#pragma unroll
-          for (int s = 1; s < t; ++s) (s & 1 ? x0 : x1) -= mrow[s] * bw[s];
-          const float wt = c16 < t ? x0 + x1 : 0.f;
-          sW[(16 * q4 + t) * MRS + 16 * q4 + c16] = wt;
-          bw[t] = be[t] * wt;
+          for (int s = 1; s < t; ++s) (s & 1 ? x0 : x1) -= Mb[t * MRS + s] * bw[s];
+          const double wt = c16 < t ? x0 + x1 : 0.0;
+          Wb[t * MRS + c16] = wt;
+          bw[t] = (double)be[t] * wt;
         }
       }
       __syncthreads();
       fresh_lane();
       // ... then the blocks below the diagonal, I rows and J columns of a pair of
       // neighbouring blocks: P = M_IJ (1 - beta W)_JJ, W_IJ = (1 - W_II beta) P
-      auto row4 = [&](const float* m, int bi, int bj) __attribute__((always_inline)) -> f32x4 {
-        const float4 x = *reinterpret_cast<const float4*>(m + (16 * bi + c16) * MRS + 16 * bj + 4 * q4);
-        return f32x4{x.x, x.y, x.z, x.w};
+      auto tile = [&](int bi, int bj) __attribute__((always_inline)) -> int {
+        return (bi * (bi + 1) / 2 + bj) * MTS;
       };
-      auto tile4 = [&](const float* m, int bi, int bj) __attribute__((always_inline)) -> f32x4 {
-        f32x4 x;
+      auto row4 = [&](const double* m, int bi, int bj) __attribute__((always_inline)) -> f64x4 {
+        const double* x = m + tile(bi, bj) + c16 * MRS + q4;
+        return f64x4{x[0], x[4], x[8], x[12]};
+      };
+      auto tile4 = [&](const double* m, int bi, int bj) __attribute__((always_inline)) -> f64x4 {
+        const double* x = m + tile(bi, bj) + q4 * MRS + c16;
+        return f64x4{x[0], x[4 * MRS], x[8 * MRS], x[12 * MRS]};
+      };
+      auto beta4 = [&](int b) __attribute__((always_inline)) -> f64x4 {
+        const float* x = sBeta + 16 * b + q4;
+        return f64x4{(double)x[0], (double)x[4], (double)x[8], (double)x[12]};
+      };
+      auto put4 = [&](int bi, int bj, const f64x4& x) __attribute__((always_inline)) {
+        double* y = sW + tile(bi, bj) + q4 * MRS + c16;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = m[(16 * bi + 4 * q4 + r) * MRS + 16 * bj + c16];
-        return x;
+        for (int r = 0; r < 4; ++r) y[4 * r * MRS] = x[r];
       };
-      auto beta4 = [&](int b) __attribute__((always_inline)) -> f32x4 {
-        const float4 x = *reinterpret_cast<const float4*>(sBeta + 16 * b + 4 * q4);
-        return f32x4{x.x, x.y, x.z, x.w};
-      };
-      auto put4 = [&](int bi, int bj, const f32x4& x) __attribute__((always_inline)) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sW[(16 * bi + 4 * q4 + r) * MRS + 16 * bj + c16] = x[r];
-      };
+      constexpr f64x4 zero4 = {0.0, 0.0, 0.0, 0.0};
       if (wv < 2) {
         const int J = 2 * wv, I = J + 1;
-        f32x4 pq = {0.f, 0.f, 0.f, 0.f}, wq = {0.f, 0.f, 0.f, 0.f};
+        f64x4 pq = zero4, wq = zero4;
         mma16(pq, row4(sM, I, J), beta4(J) * tile4(sW, J, J));
         pq = tile4(sM, I, J) - pq;
         mma16(wq, row4(sW, I, I), beta4(I) * pq);
@@ -522,16 +532,16 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
       __syncthreads();
       if (wv < 2) {  // 32 x 32 blocks: wave tj takes columns 16 tj ..
         const int tj = wv;
-        f32x4 p0 = {0.f, 0.f, 0.f, 0.f}, p1 = p0;
+        f64x4 p0 = zero4, p1 = zero4;
         for (int kb = tj; kb < 2; ++kb) {
-          const f32x4 b = beta4(kb) * tile4(sW, kb, tj);
+          const f64x4 b = beta4(kb) * tile4(sW, kb, tj);
           mma16(p0, row4(sM, 2, kb), b);
           mma16(p1, row4(sM, 3, kb), b);
         }
         p0 = tile4(sM, 2, tj) - p0;
         p1 = tile4(sM, 3, tj) - p1;
-        f32x4 w0 = {0.f, 0.f, 0.f, 0.f}, w1 = w0;
-        const f32x4 b0p = beta4(2) * p0;
+        f64x4 w0 = zero4, w1 = zero4;
+        const f64x4 b0p = beta4(2) * p0;
         mma16(w0, row4(sW, 2, 2), b0p);
         mma16(w1, row4(sW, 3, 2), b0p);
         mma16(w1, row4(sW, 3, 3), beta4(3) * p1);
@@ -546,13 +556,17 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
       // 8 consecutive-pair elements of W beta's row t = 16 i + c16 for K step kk
       // (tokens 32 kk + 4 q4 + e and 16 further), zero for tokens before lo
       auto wrow = [&](int i, int kk, int lo) __attribute__((always_inline)) -> f32x8 {
-        const float* wp = sW + (16 * i + c16) * MRS + 32 * kk + 4 * q4;
-        const float4 wa = *reinterpret_cast<const float4*>(wp);
-        const float4 wb = *reinterpret_cast<const float4*>(wp + 16);
-        const float4 ba = *reinterpret_cast<const float4*>(sBeta + 32 * kk + 4 * q4);
-        const float4 bb = *reinterpret_cast<const float4*>(sBeta + 32 * kk + 16 + 4 * q4);
-        f32x8 x = {wa.x * ba.x, wa.y * ba.y, wa.z * ba.z, wa.w * ba.w,
-                   wb.x * bb.x, wb.y * bb.y, wb.z * bb.z, wb.w * bb.w};
+        f32x8 x;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const bool in = 2 * kk + j <= i;  // (else above the diagonal)
+          const double* wp = sW + (in ? tile(i, 2 * kk + j) : 0) + c16 * MRS + 4 * q4;
+          const float4 b = *reinterpret_cast<const float4*>(sBeta + 32 * kk + 16 * j + 4 * q4);
+          x[4 * j] = in ? (float)(wp[0] * (double)b.x) : 0.f;
+          x[4 * j + 1] = in ? (float)(wp[1] * (double)b.y) : 0.f;
+          x[4 * j + 2] = in ? (float)(wp[2] * (double)b.z) : 0.f;
+          x[4 * j + 3] = in ? (float)(wp[3] * (double)b.w) : 0.f;
+        }
 #pragma unroll
         for (int e = 0; e < 8; ++e)
           if (32 * kk + 16 * (e >> 2) + 4 * q4 + (e & 3) < lo) x[e] = 0.f;
@@ -570,10 +584,12 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
 #pragma unroll
           for (int i = 2 * kk; i < 4; ++i) {
             const XT wa(wrow(i, kk, 0));
+            f32x4 y = {0.f, 0.f, 0.f, 0.f};
             if constexpr (P::E == 2)
-              mma16_split(Y[i], wa, zb);
+              mma16_split(y, wa, zb);
             else
-              mma16(Y[i], wa, zb);
+              mma16(y, wa, zb);
+            Y[i] += y;
           }
         }
         // the wave's shares of y . v and |y|^2, summed over its 16 columns
@@ -600,26 +616,24 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
 
       fresh_lane();
       // ------------------------------------------------------- decisions
-      RowIn rin;
+      RowIn<double> rin;
       rin.nrow = nrow;
       rin.C = C;
-      rin.D = (float)D;
       rin.tau = a.tau;
       rin.eps = a.eps;
-      rin.eps_rms = a.eps_rms;
-      const float kk2 = sKK[lane], vv2 = sV2[lane], bet = sBeta[lane];
-      rin.a = kk2 * vv2;
-      rin.al2n = (lane + 1 < SL) ? sAl2[lane + 1] : 0.f;
+      const double kk2 = sKK[lane], vv2 = sV2[lane], bet = (double)sBeta[lane];
+      rin.sc = ScoreIn<double>::of((double)a.eps_rms, (double)D, kk2 * vv2);
+      rin.al2n = (lane + 1 < SL) ? sAl2[lane + 1] : 0.0;
       rin.bo = sBo[lane];
       // growth of |S|^2 with a token of y . v = c and |y|^2 = q: S + k u^T, u =
       // beta (v - y)
-      auto grow = [&](float c, float q) __attribute__((always_inline)) -> float {
-        const float u2 = vv2 - 2.f * c + q;
-        return 2.f * bet * (c - q) + kk2 * bet * bet * (u2 < 0.f ? 0.f : u2);
+      auto grow = [&](double c, double q) __attribute__((always_inline)) -> double {
+        const double u2 = vv2 - 2.0 * c + q;
+        return 2.0 * bet * (c - q) + kk2 * bet * bet * (u2 < 0.0 ? 0.0 : u2);
       };
-      auto row = [&](int p, float& ct, float& inc) __attribute__((always_inline)) {
-        ct = (lane > p) ? sR[lane * RRS + p] : 0.f;
-        inc = grow(ct, (lane > p) ? sQ[lane * RRS + p] : 0.f);
+      auto row = [&](int p, double& ct, double& inc) __attribute__((always_inline)) {
+        ct = (lane > p) ? (double)sR[lane * RRS + p] : 0.0;
+        inc = grow(ct, (lane > p) ? (double)sQ[lane * RRS + p] : 0.0);
       };
       if (wv == 0) {
         if (dec.m == 0) {
@@ -632,17 +646,17 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         }
         const bool more = dec.first_rows(
             rin, 1,
-            [&](int p, float& ct, float& inc, float& binit) __attribute__((always_inline)) {
+            [&](int p, double& ct, double& inc, double& binit) __attribute__((always_inline)) {
               // (an empty cache's first token starts from S = 0)
-              float c = 0.f, q = 0.f;
+              double c = 0.0, q = 0.0;
 #pragma unroll
               for (int i = 0; i < NW; ++i) {
-                c += sPc[i * SL + lane];
-                q += sPq[i * SL + lane];
+                c += (double)sPc[i * SL + lane];
+                q += (double)sPq[i * SL + lane];
               }
               ct = c;
               inc = grow(c, q);
-              binit = sA[0] * sA[0] * b0;
+              binit = sAl2[0] * b0;
             },
             open_at);
         if (lane == 0) {
@@ -663,46 +677,37 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           if (x >= 10) break;
           const int tr = x < 1 ? 0 : (x < 3 ? 1 : (x < 6 ? 2 : 3));
           const int tc = x - tr * (tr + 1) / 2;
-          f32x4 z = {0.f, 0.f, 0.f, 0.f};
+          f64x4 z = zero4;
           for (int kb = tc; kb <= tr; ++kb) {
-            f32x4 b = tile4(sVV, kb, tc);  // rows r' of block kb, column r
+            f64x4 b = tile4(sVV, kb, tc);  // rows r' of block kb, column r
             if (kb == tc) {
 #pragma unroll
               for (int r = 0; r < 4; ++r)
-                if (4 * q4 + r <= c16) b[r] = 0.f;
+                if (4 * r + q4 <= c16) b[r] = 0.0;
             }
             mma16(z, row4(sW, tr, kb) * beta4(kb), b);
           }
-          const float br = sBeta[16 * tc + c16], vr2 = sV2[16 * tc + c16];
+          const double br = (double)sBeta[16 * tc + c16], vr2 = sV2[16 * tc + c16];
+          const f64x4 wt = tile4(sW, tr, tc);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int t = 16 * tr + 4 * q4 + r;
-            const float xr = sW[t * MRS + 16 * tc + c16] * br;
-            sQ[t * RRS + 16 * tc + c16] = xr * (2.f * z[r] + vr2 * xr);
+            const double xr = wt[r] * br;
+            sQ[(16 * tr + 4 * r + q4) * RRS + 16 * tc + c16] = (float)(xr * (2.0 * z[r] + vr2 * xr));
           }
         }
         __syncthreads();
         {
           const int s = SL - 1 - lane;  // the suffix sum over s is a prefix sum over the lanes
-          const float bs = sBeta[s];
+          const double bs = (double)sBeta[s];
 #pragma unroll
           for (int t = wv; t < SL; t += SWAVE) {
-            float x = (s < t) ? sW[t * MRS + s] * bs * sVV[t * MRS + s] : 0.f;
-            float y = (s < t) ? sQ[t * RRS + s] : 0.f;
-            x += dpp_f<0x111, 0xF>(0.f, x);
-            y += dpp_f<0x111, 0xF>(0.f, y);
-            x += dpp_f<0x112, 0xF>(0.f, x);
-            y += dpp_f<0x112, 0xF>(0.f, y);
-            x += dpp_f<0x114, 0xF>(0.f, x);
-            y += dpp_f<0x114, 0xF>(0.f, y);
-            x += dpp_f<0x118, 0xF>(0.f, x);
-            y += dpp_f<0x118, 0xF>(0.f, y);
-            x += dpp_f<0x142, 0xA>(0.f, x);
-            y += dpp_f<0x142, 0xA>(0.f, y);
-            x += dpp_f<0x143, 0xC>(0.f, x);
-            y += dpp_f<0x143, 0xC>(0.f, y);
-            sR[t * RRS + s] = x;
-            sQ[t * RRS + s] = y;
+            const int at = tile(t >> 4, min(s, t) >> 4) + (t & 15) * MRS + (s & 15);
+            double x = (s < t) ? sW[at] * bs * sVV[at] : 0.0;
+            double y = (s < t) ? (double)sQ[t * RRS + s] : 0.0;
+            wave_prefix_d(x);
+            wave_prefix_d(y);
+            sR[t * RRS + s] = (float)x;
+            sQ[t * RRS + s] = (float)y;
           }
         }
         __syncthreads();
@@ -711,9 +716,9 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           if (!dense)
             more = dec.first_rows(
                 rin, NSEQ - 1,
-                [&](int p, float& ct, float& inc, float& binit) __attribute__((always_inline)) {
+                [&](int p, double& ct, double& inc, double& binit) __attribute__((always_inline)) {
                   row(p, ct, inc);
-                  binit = 0.f;
+                  binit = 0.0;
                 },
                 open_at);
           if (lane == 0) sMisc[3] = more ? dec.p : -1;
@@ -786,7 +791,8 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
             const float4 x = *reinterpret_cast<const float4*>(sDe + 16 * i + 4 * q4);
             return f32x4{x.x, x.y, x.z, x.w};
           }();
-          const f32x4 u = beta4(i) * (Vr[i] - Y[i]);
+          const float4 bi = *reinterpret_cast<const float4*>(sBeta + 16 * i + 4 * q4);
+          const f32x4 u = f32x4{bi.x, bi.y, bi.z, bi.w} * (Vr[i] - Y[i]);
           ud[i] = u * de;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {

@@ -488,20 +488,18 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
         }
       }
     }
-    RowIn rin;
+    RowIn<float> rin;
     rin.nrow = nrow;
     rin.C = C;
-    rin.D = Df;
     rin.tau = tau;
     rin.eps = a.eps;
-    rin.eps_rms = a.eps_rms;
-    rin.a = sa[lane];
+    rin.sc = ScoreIn<float>{a.eps_rms, Df, sa[lane]};
     rin.al2n = (lane + 1 < SL) ? sAl2[lane + 1] : 0.f;
     rin.bo = sBo[lane];
     // c and growth 2 c + a of |S|^2 for a state that began at p >= 0 of the chunk
     auto row = [&](int p, float& ct, float& inc) __attribute__((always_inline)) {
       ct = (lane > p) ? sR[lane * (SL + 1) + p] : 0.f;
-      inc = 2.f * ct + rin.a;
+      inc = 2.f * ct + rin.sc.a;
     };
     auto open_at = [&](int ts, float Is) __attribute__((always_inline)) {
       dec.open(ts, Is, mforce, c0, C, T, &reinterpret_cast<CacheHeader*>(a.cache)->flags,
@@ -529,7 +527,7 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
             binit = 0.f;
             if (p < 0) {
               ct = At * c0t + sR[lane * (SL + 1)];  // R[0][t]
-              inc = 2.f * ct + rin.a;
+              inc = 2.f * ct + rin.sc.a;
               binit = sA[0] * sA[0] * b0;
             } else {
               row(p, ct, inc);

@@ -252,34 +252,80 @@ struct StatesInLds {
   }
 };
 
-// Scan-chunk constants of the lane's token, and of the layer.
+// The score's part that does not depend on the row, and the score of the token
+// against a state of |S|^2 = b, k^T S v = c.
+template <typename N>
+struct ScoreIn;
+template <>
+struct ScoreIn<float> {
+  float eps_rms, D;
+  float a;  // |k|^2 |v|^2
+  __device__ __forceinline__ float at(float b, float c, float eps) const {
+    return score_f(a, b, c, D, eps, eps_rms);
+  }
+};
+// The delta form: the three terms of |N(s) - N(S)|^2, which cancel where the token
+// fits the state, in float64.
+template <>
+struct ScoreIn<double> {
+  double eps_rms, rD;
+  double na, ra;  // a / rs^2, 1 / rs
+  __device__ static __forceinline__ double rsq(double x) {  // two Newton steps
+    double r = __builtin_amdgcn_rsq(x);
+    r = r * (1.5 - 0.5 * x * r * r);
+    return r * (1.5 - 0.5 * x * r * r);
+  }
+  __device__ static __forceinline__ ScoreIn of(double eps_rms, double D, double a) {
+    ScoreIn s;
+    s.eps_rms = eps_rms;
+    s.rD = 1.0 / D;
+    s.ra = rsq(a * s.rD + eps_rms);
+    s.na = a * s.ra * s.ra;
+    return s;
+  }
+  __device__ __forceinline__ float at(double b, double c, float eps) const {
+    const double r = rsq(b * rD + eps_rms);
+    const double nb = b * r * r;
+    const float num = (float)(na + nb - 2.0 * c * ra * r);
+    return sqrtf(num < 0.f ? 0.f : num) / (sqrtf((float)nb) + eps);
+  }
+};
+
+// Scan-chunk constants of the lane's token, and of the layer.  N: the type of
+// |S|^2's recurrence (float64 in the delta form, whose steps can also shrink it).
+template <typename N>
 struct RowIn {
-  float a;      // |k|^2 |v|^2
-  float al2n;   // alpha^2 of the next token
+  ScoreIn<N> sc;
+  N al2n;       // alpha^2 of the next token
   int bo;       // boundary override
   int nrow, C;
-  float D, tau, eps, eps_rms;
+  float tau, eps;
 };
 
 // Row p: the score of the lane's token against the newest state that began at
 // p, with c = k^T S v of the decayed state and |S|^2 growing by inc when the
 // token joins: b(t + 1) = alpha_{t+1}^2 (b(t) + inc(t)), b(start) = binit.
 // Returns whether the token is scored by this row and opens a state.
-__device__ __forceinline__ bool score_row(const RowIn& x, int t, int p, float ct, float inc,
-                                          float binit, float& It, bool& valid) {
+template <typename N>
+__device__ __forceinline__ bool score_row(const RowIn<N>& x, int t, int p, N ct, N inc,
+                                          N binit, float& It, bool& valid) {
   const int ustart = p < 0 ? 0 : p;
-  float Am = 1.f, Bm = 0.f;
+  N Am = 1, Bm = 0;
   if (t >= ustart) {
     Am = x.al2n;
     Bm = x.al2n * inc;
   }
   // inclusive scan of the affine maps b -> Am b + Bm over the lanes
   wave_scan_affine(Am, Bm);
-  const float bnext = Am * binit + Bm;         // b(t + 1)
-  float bt = dpp_f<0x138, 0xF>(binit, bnext);  // lane t - 1
+  const N bnext = Am * binit + Bm;  // b(t + 1)
+  N bt;                             // lane t - 1
+  if constexpr (sizeof(N) == 8)
+    bt = dpp_d<0x138, 0xF>(binit, bnext);
+  else
+    bt = dpp_f<0x138, 0xF>(binit, bnext);
   if (t == ustart) bt = binit;
   valid = t < x.nrow && t > p;
-  It = valid ? score_f(x.a, bt, ct, x.D, x.eps, x.eps_rms) : 0.f;
+  It = valid ? x.sc.at(bt, ct, x.eps) : 0.f;
   int bd = (It >= x.tau) ? 1 : 0;
   if (x.bo != -1) bd = x.bo ? 1 : 0;
   if (x.C == 1) bd = 0;
@@ -305,8 +351,8 @@ struct RowTables {
 
 // Rows p0 .. nrow - 1, one workgroup; row(p, ct, inc) gives the lane's c and
 // growth for a state that began at p.
-template <typename RowFn>
-__device__ __forceinline__ void fill_rows(const RowIn& x, int p0, RowTables tb, RowFn row) {
+template <typename N, typename RowFn>
+__device__ __forceinline__ void fill_rows(const RowIn<N>& x, int p0, RowTables tb, RowFn row) {
   const int t = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
   auto finish = [&](int p, bool open, float It) __attribute__((always_inline)) {
@@ -323,12 +369,13 @@ __device__ __forceinline__ void fill_rows(const RowIn& x, int p0, RowTables tb, 
   // two rows at a time, so that their chains overlap
   for (int p = p0 + wv; p < x.nrow; p += 2 * SWAVE) {
     const int q = min(p + SWAVE, SL - 1);
-    float cp, ip, cq, iq, Ip, Iq;
+    float Ip, Iq;
+    N cp, cq, ip, iq;
     bool vp, vq;
     row(p, cp, ip);
     row(q, cq, iq);
-    const bool op = score_row(x, t, p, cp, ip, 0.f, Ip, vp);
-    const bool oq = score_row(x, t, q, cq, iq, 0.f, Iq, vq);
+    const bool op = score_row(x, t, p, cp, ip, N(0), Ip, vp);
+    const bool oq = score_row(x, t, q, cq, iq, N(0), Iq, vq);
     finish(p, op, Ip);
     if (p + SWAVE < x.nrow) finish(p + SWAVE, oq, Iq);
   }
@@ -386,12 +433,14 @@ struct ChunkDecider {
   // Rows one at a time until the chunk ends (returns false) or nseq boundaries
   // were taken with tokens left (returns true; fill_rows and finish_rows go on
   // from p).  row(p, ct, inc, binit) as for fill_rows.
-  template <typename RowFn, typename OpenFn>
-  __device__ __forceinline__ bool first_rows(const RowIn& x, int nseq, RowFn row, OpenFn open_at) {
+  template <typename N, typename RowFn, typename OpenFn>
+  __device__ __forceinline__ bool first_rows(const RowIn<N>& x, int nseq, RowFn row,
+                                             OpenFn open_at) {
     const int t = threadIdx.x & 63;
     int taken = 0;
     while (p + 1 < x.nrow) {
-      float ct, inc, binit, It;
+      float It;
+      N ct, inc, binit;
       bool valid;
       row(p, ct, inc, binit);
       const bool op = score_row(x, t, p, ct, inc, binit, It, valid);
@@ -408,8 +457,8 @@ struct ChunkDecider {
   }
 
   // The rest of the chunk from the tables of fill_rows(p0 = p).
-  template <typename OpenFn>
-  __device__ __forceinline__ void finish_rows(const RowIn& x, RowTables tb, OpenFn open_at) {
+  template <typename N, typename OpenFn>
+  __device__ __forceinline__ void finish_rows(const RowIn<N>& x, RowTables tb, OpenFn open_at) {
     const int t = threadIdx.x & 63;
     const int p0 = p;
     const int tt = min(max(t, p0), x.nrow - 1);  // (rows before p0 hold nothing)

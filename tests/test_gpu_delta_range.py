@@ -56,3 +56,40 @@ def test_steep_gates(dtype, dk, dv, gate, expanding):
     if expanding:
         beta[:, 150] = 1.0
     _check(w, x, beta, what=f"gate {gate} {dtype} {expanding}", max_frac=0.02)
+
+
+@pytest.mark.parametrize("dtype,dk,dv", [("f32", 128, 128), ("f32", 64, 64), ("bf16", 128, 64)])
+@pytest.mark.parametrize("lo,hi", [(0.05, 1.0), (1.8, 2.0)])
+def test_float32_precision(dtype, dk, dv, lo, hi):
+    """Scores and the newest state to float32 rounding.  A token by token scan
+    in float32 is off by up to 5.5e-7 in the score (2^-24 of the three terms of
+    the difference, each near D, over twice a score of about 0.1) and 3.8e-7 in
+    the state; twice that is allowed."""
+    import torch
+    from paper_2606_10650_amd import dla
+    T, n = 330, 8
+    w = WORKLOADS["cfg2"].replace(B=1, H=n, T=T, C=40, dk=dk, dv=dv, dtype=dtype, mean_len=30.0,
+                                  seed=17 + dk)
+    x = make_inputs(w)
+    beta = np.random.default_rng(dk).uniform(lo, hi, (n, T)).astype(np.float32)
+    xf = H.f64(x, w)
+    bo = np.full((n, T), 0, np.int8)              # forced: the states are the oracle's
+    bo[:, 25::31] = 1
+    ref = oracle_forward(xf["k"], xf["v"], xf["g"], w.C, w.tau, q=xf["q"], lam=xf["lam"],
+                         beta=beta.astype(np.float64), b_override=bo)
+    _, k, v, g, _ = H.inputs_to_device(w, x, 1, n)
+    cache = dla.cache_alloc(1, n, w.C, dk, dv, device="cuda")
+    dev = lambda a: torch.from_numpy(a).reshape(1, n, T).cuda()  # noqa: E731
+    s = dla.prefill_delta(cache, None, k, v, g, dev(beta), None, tau=w.tau, skip_readout=True,
+                          boundary_override=dev(bo))[3].cpu().numpy().reshape(n, T)
+    err = np.abs(s - ref["score"]) / np.maximum(ref["score"], 1.0)
+    S = H.true_states(dla.cache_export(cache))
+    worst = 0.0
+    for h in range(n):
+        m = int(ref["cache"].m[h])
+        Sr = ref["cache"].S[h, m - 1]
+        worst = max(worst, np.linalg.norm(S[h, m - 1] - Sr) / np.linalg.norm(Sr))
+    print(f"[precision] {dtype} {dk}x{dv} beta {lo}..{hi}: score {err.max():.2e} state {worst:.2e}",
+          flush=True)
+    assert err.max() < 1.1e-6
+    assert worst < 8e-7
