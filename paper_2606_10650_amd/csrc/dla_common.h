@@ -193,20 +193,23 @@ __device__ __forceinline__ void wave_scan_affine(float& A, float& B) {
   affine_step<0x143, 0xC>(A, B);
 }
 
+// In float64, and beside it the scan of x -> A x + S.
 template <int CTRL, int RMASK>
-__device__ __forceinline__ void affine_step(double& A, double& B) {
+__device__ __forceinline__ void affine_step(double& A, double& B, float& S) {
   const double Ao = dpp_d<CTRL, RMASK>(1.0, A);
   const double Bo = dpp_d<CTRL, RMASK>(0.0, B);
+  const float So = dpp_f<CTRL, RMASK>(0.f, S);
   B = __builtin_fma(A, Bo, B);
+  S = (float)A * So + S;
   A = A * Ao;
 }
-__device__ __forceinline__ void wave_scan_affine(double& A, double& B) {
-  affine_step<0x111, 0xF>(A, B);
-  affine_step<0x112, 0xF>(A, B);
-  affine_step<0x114, 0xF>(A, B);
-  affine_step<0x118, 0xF>(A, B);
-  affine_step<0x142, 0xA>(A, B);
-  affine_step<0x143, 0xC>(A, B);
+__device__ __forceinline__ void wave_scan_affine(double& A, double& B, float& S) {
+  affine_step<0x111, 0xF>(A, B, S);
+  affine_step<0x112, 0xF>(A, B, S);
+  affine_step<0x114, 0xF>(A, B, S);
+  affine_step<0x118, 0xF>(A, B, S);
+  affine_step<0x142, 0xA>(A, B, S);
+  affine_step<0x143, 0xC>(A, B, S);
 }
 
 // Sum of a float over the wavefront through DPP row shifts and broadcasts

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
   int32_t* sMisc = sBo + SL;
   // sMisc: 0, 1 boundary mask; 2 start of the rows left (-1: none); 3 go on with
   // the row tables; 4, 5 non-finite inputs of an even, an odd chunk; 6 the
-  // decision of the token by token path
+  // decision of the token by token path; 7 tokens that the rows decided
   __shared__ double sGlast[1];
 
   Meta M = meta_at(a.cache + a.meta_offset + (size_t)h * a.meta_stride, C);
@@ -367,7 +367,8 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     // Token by token when an input of the chunk or the state is not finite, or
     // when a token's step is not a contraction (beta |k|^2 outside [0, 2]): the
     // tables range over starts that the boundaries may exclude, and only
-    // contractions bound them.
+    // contractions bound them.  And from a token whose step erases the state, so
+    // that |S|^2 is lost in the rounding of its terms (score_row).
     float kk = 0.f;
 #pragma unroll
     for (int i = 0; i < SWAVE; ++i) kk += sPq[i * SL + lane];
@@ -386,17 +387,20 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     const bool dense = __popcll(dec.B) >= NSEQ;  // (wave 0)
     if (wv == 0) {
       dec.p = -1;
+      dec.tn = nrow;
       dec.B = 0;
       dec.mo = -1;
       dec.dc = -1;
       dec.io = 0.f;
     }
 
-    if (!serial) {
+    int tn = 0;  // tokens taken together; the others follow one by one
+    bool together = !serial;
+    f32x4 X[4];   // X[i][r]: token 16 i + 4 q4 + r, column col
+    f32x4 Vr[4];  // the values in the same layout
+    if (together) {
       fresh_lane();
       // ------------------------------------ Gram products, and the carry S^T k
-      f32x4 X[4];   // X[i][r]: token 16 i + 4 q4 + r, column col
-      f32x4 Vr[4];  // the values in the same layout
 #pragma unroll
       for (int i = 0; i < 4; ++i) X[i] = Vr[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       // the 10 + 10 lower 16 x 16 tiles of K K^T and V V^T, dealt to the waves
@@ -470,7 +474,10 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         }
       }
       __syncthreads();
-
+      // (a value whose square overflows float32 would spoil the sums of others)
+      together = __ballot(is_bad((float)sV2[lane])) == 0;  // (workgroup-uniform)
+    }
+    if (together) {
       fresh_lane();
       // ---------------------------------- W: y_t = sum_{r<t} W[t][r] beta_r v_r
       // W[t][r] = M[t][r] - sum_{r<s<t} M[t][s] beta_s W[s][r]: within the 16 x 16
@@ -663,6 +670,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           sMisc[0] = (int)(uint32_t)dec.B;
           sMisc[1] = (int)(uint32_t)(dec.B >> 32);
           sMisc[2] = more ? dec.p : -1;
+          sMisc[7] = dec.tn;
         }
       }
       __syncthreads();
@@ -733,6 +741,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         if (wv == 0 && lane == 0) {
           sMisc[0] = (int)(uint32_t)dec.B;
           sMisc[1] = (int)(uint32_t)(dec.B >> 32);
+          sMisc[7] = dec.tn;
         }
         __syncthreads();
       }
@@ -746,7 +755,12 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         return x ? 63 - __clzll((long long)x) : -1;
       };
       const int plast = start_of(SL - 1);
-      if (own) {
+      tn = __builtin_amdgcn_readfirstlane(sMisc[7]);
+      if (tn > 0 && tn < nrow) {  // (workgroup-uniform) decays to the last of the tokens taken
+        if (tid < SL) sDe[tid] = tid < tn ? (float)exp_gate(sG[tn - 1] - sG[tid]) : 0.f;
+        __syncthreads();
+      }
+      if (own && tn > 0) {
         if (B) {
           // tokens whose state began in the chunk: Y = (W beta) V over its tokens
           f32x4 Z[4];
@@ -781,7 +795,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         }
         fresh_lane();
         const int s0 = plast < 0 ? 0 : plast;
-        const float sc = (plast < 0) ? sA[nrow - 1] : 0.f;
+        const float sc = (plast < 0) ? sA[tn - 1] : 0.f;
 #pragma unroll
         for (int i = 0; i < NI; ++i) S[i] *= sc;
         f32x4 ud[4];
@@ -798,7 +812,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           for (int r = 0; r < 4; ++r) {
             const int t = 16 * i + 4 * q4 + r;
             if (t < s0) ud[i][r] = 0.f;
-            if (t < nrow) {
+            if (t < tn) {
               Uh[(size_t)(c0 + t) * DV + col] = u[r];
               if (U16h) U16h[(size_t)(c0 + t) * DV + col] = from_f32<bf16_t>(u[r]);
             }
@@ -806,7 +820,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         }
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-          if (32 * kk + 31 < s0 || 32 * kk >= nrow) continue;  // (uniform)
+          if (32 * kk + 31 < s0 || 32 * kk >= tn) continue;  // (uniform)
           f32x8 z;
 #pragma unroll
           for (int e = 0; e < 8; ++e) z[e] = ud[2 * kk + (e >> 2)][e & 3];
@@ -827,10 +841,22 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           }
         }
       }
-    } else {
+      if (tn < nrow) {  // the values again, over sQ
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < V16; ++u) {
+          const int pi = tid + STHR * u;
+          const int r = pi % SL, pc = pi / SL;
+          *reinterpret_cast<u32x4*>(sV + r * VRS + pc * P::EPP) =
+              reinterpret_cast<const u32x4*>(Vin + (size_t)(c0 + min(r, nrow - 1)) * DV)[pc];
+        }
+        __syncthreads();
+      }
+    }
+    if (tn < nrow) {
       fresh_lane();
       // ---------------------------------------------------- token by token
-      for (int t = 0; t < nrow; ++t) {
+      for (int t = tn; t < nrow; ++t) {
         float y = 0.f, b = 0.f, kr[NI][4];
         const float vt = own ? to_f32(sV[t * VRS + col]) : 0.f;
         if (own) {

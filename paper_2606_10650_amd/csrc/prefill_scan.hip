@@ -508,6 +508,7 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
     if (wv == 0) {
       const int nseq = __popcll(dec.B) >= NSEQ ? 1 : NSEQ;
       dec.p = -1;
+      dec.tn = nrow;  // (no token is lost in the gated form)
       dec.B = 0;
       dec.mo = -1;
       dec.dc = -1;

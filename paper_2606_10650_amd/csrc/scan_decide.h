@@ -302,29 +302,44 @@ struct RowIn {
   float tau, eps;
 };
 
+// |S|^2 as a share of the sum of its terms' sizes below which a row stops: the
+// terms carry float32 roundings, so that above it |S|^2 is good to 16 x 2^-24.  Every
+// token of ordinary prompts (beta in (0, 1), one state per 30 or more tokens) is
+// above 1/8, with beta in 1.8 .. 2 above 1/16.
+constexpr float kLost = 1.f / 16;
+
 // Row p: the score of the lane's token against the newest state that began at
 // p, with c = k^T S v of the decayed state and |S|^2 growing by inc when the
 // token joins: b(t + 1) = alpha_{t+1}^2 (b(t) + inc(t)), b(start) = binit.
-// Returns whether the token is scored by this row and opens a state.
+// Returns whether the token is scored by this row and opens a state.  lost: the
+// token is scored by this row, but too little is left of the terms of its b for
+// their sum to hold |S|^2 (delta form, whose inc may be negative).
 template <typename N>
 __device__ __forceinline__ bool score_row(const RowIn<N>& x, int t, int p, N ct, N inc,
-                                          N binit, float& It, bool& valid) {
+                                          N binit, float& It, bool& valid, bool& lost) {
   const int ustart = p < 0 ? 0 : p;
   N Am = 1, Bm = 0;
   if (t >= ustart) {
     Am = x.al2n;
     Bm = x.al2n * inc;
   }
-  // inclusive scan of the affine maps b -> Am b + Bm over the lanes
-  wave_scan_affine(Am, Bm);
-  const N bnext = Am * binit + Bm;  // b(t + 1)
-  N bt;                             // lane t - 1
-  if constexpr (sizeof(N) == 8)
-    bt = dpp_d<0x138, 0xF>(binit, bnext);
-  else
-    bt = dpp_f<0x138, 0xF>(binit, bnext);
-  if (t == ustart) bt = binit;
   valid = t < x.nrow && t > p;
+  // inclusive scan of the affine maps b -> Am b + Bm over the lanes
+  N bt;  // b(t) = b(lane t - 1's t + 1)
+  if constexpr (sizeof(N) == 8) {
+    float Sm = fabsf((float)Bm);  // the same sum over |inc|
+    wave_scan_affine(Am, Bm, Sm);
+    bt = dpp_d<0x138, 0xF>(binit, Am * binit + Bm);
+    float st = dpp_f<0x138, 0xF>((float)binit, (float)(Am * binit) + Sm);
+    if (t == ustart) st = (float)binit;
+    if (t == ustart) bt = binit;
+    lost = valid && !(bt >= (double)(kLost * st) && bt < 3.4e38);
+  } else {
+    wave_scan_affine(Am, Bm);
+    bt = dpp_f<0x138, 0xF>(binit, Am * binit + Bm);
+    if (t == ustart) bt = binit;
+    lost = false;
+  }
   It = valid ? x.sc.at(bt, ct, x.eps) : 0.f;
   int bd = (It >= x.tau) ? 1 : 0;
   if (x.bo != -1) bd = x.bo ? 1 : 0;
@@ -333,9 +348,11 @@ __device__ __forceinline__ bool score_row(const RowIn<N>& x, int t, int p, N ct,
 }
 
 // LDS tables of the rows evaluated by all waves: scores [p][t], and per row the
-// next boundary, its score and the sum of the scores of the tokens before it.
+// next boundary, its score and the sum of the scores of the tokens before it (or,
+// with kStop added, the token before the first lost one if that comes no later).
 struct RowTables {
   static constexpr int STRIDE = SL + 1;
+  static constexpr int kStop = 256;
   float* It;     // [SL][STRIDE]
   double* sum;   // [SL]
   int32_t* nx;   // [SL]
@@ -355,13 +372,15 @@ template <typename N, typename RowFn>
 __device__ __forceinline__ void fill_rows(const RowIn<N>& x, int p0, RowTables tb, RowFn row) {
   const int t = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
-  auto finish = [&](int p, bool open, float It) __attribute__((always_inline)) {
-    const uint64_t mask = __ballot(open);
+  auto finish = [&](int p, bool open, bool lost, float It) __attribute__((always_inline)) {
+    const uint64_t mask = __ballot(open), lmask = __ballot(lost);
     const int ts = mask ? (__ffsll((unsigned long long)mask) - 1) : x.nrow;
-    const double s = wave_sum_d((t > p && t < ts) ? (double)It : 0.0);
+    const int tl = lmask ? (__ffsll((unsigned long long)lmask) - 1) : SL + 1;
+    const int e = tl <= ts ? max(tl - 1, p + 1) : ts;
+    const double s = wave_sum_d((t > p && t < e) ? (double)It : 0.0);
     tb.It[p * RowTables::STRIDE + t] = It;
     if (t == 0) {
-      tb.nx[p] = ts;
+      tb.nx[p] = tl <= ts ? e + RowTables::kStop : e;
       tb.sum[p] = s;
     }
     if (t == ts) tb.Inx[p] = It;
@@ -371,13 +390,13 @@ __device__ __forceinline__ void fill_rows(const RowIn<N>& x, int p0, RowTables t
     const int q = min(p + SWAVE, SL - 1);
     float Ip, Iq;
     N cp, cq, ip, iq;
-    bool vp, vq;
+    bool vp, vq, lp, lq;
     row(p, cp, ip);
     row(q, cq, iq);
-    const bool op = score_row(x, t, p, cp, ip, N(0), Ip, vp);
-    const bool oq = score_row(x, t, q, cq, iq, N(0), Iq, vq);
-    finish(p, op, Ip);
-    if (p + SWAVE < x.nrow) finish(p + SWAVE, oq, Iq);
+    const bool op = score_row(x, t, p, cp, ip, N(0), Ip, vp, lp);
+    const bool oq = score_row(x, t, q, cq, iq, N(0), Iq, vq, lq);
+    finish(p, op, lp, Ip);
+    if (p + SWAVE < x.nrow) finish(p + SWAVE, oq, lq, Iq);
   }
 }
 
@@ -389,6 +408,9 @@ struct ChunkDecider {
   States st;
   int m;        // states in the cache
   int p;        // where the newest state began (-1: before the chunk)
+  // tokens of the chunk that the rows decide (set to nrow before them): up to the
+  // one whose step leaves the lost |S|^2
+  int tn;
   uint64_t B;
   int mo, dc;
   float io;
@@ -430,9 +452,9 @@ struct ChunkDecider {
     p = ts;
   }
 
-  // Rows one at a time until the chunk ends (returns false) or nseq boundaries
-  // were taken with tokens left (returns true; fill_rows and finish_rows go on
-  // from p).  row(p, ct, inc, binit) as for fill_rows.
+  // Rows one at a time until the chunk or, at a lost token, the rows end (returns
+  // false) or nseq boundaries were taken with tokens left (returns true; fill_rows
+  // and finish_rows go on from p).  row(p, ct, inc, binit) as for fill_rows.
   template <typename N, typename RowFn, typename OpenFn>
   __device__ __forceinline__ bool first_rows(const RowIn<N>& x, int nseq, RowFn row,
                                              OpenFn open_at) {
@@ -441,14 +463,20 @@ struct ChunkDecider {
     while (p + 1 < x.nrow) {
       float It;
       N ct, inc, binit;
-      bool valid;
+      bool valid, lost;
       row(p, ct, inc, binit);
-      const bool op = score_row(x, t, p, ct, inc, binit, It, valid);
-      const uint64_t mask = __ballot(op);
+      const bool op = score_row(x, t, p, ct, inc, binit, It, valid, lost);
+      const uint64_t mask = __ballot(op), lmask = __ballot(lost);
       const int ts = mask ? (__ffsll((unsigned long long)mask) - 1) : x.nrow;
-      const bool joins = valid && t < ts;
+      const int tl = lmask ? (__ffsll((unsigned long long)lmask) - 1) : SL + 1;
+      const int e = tl <= ts ? max(tl - 1, p + 1) : ts;
+      const bool joins = valid && t < e;
       if (joins) io = It;
-      if (ts > p + 1) st.join(m - 1, ts - (p + 1), wave_sum_d(joins ? (double)It : 0.0));
+      if (e > p + 1) st.join(m - 1, e - (p + 1), wave_sum_d(joins ? (double)It : 0.0));
+      if (tl <= ts) {
+        tn = e;
+        return false;
+      }
       if (ts >= x.nrow) return false;
       open_at(ts, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(It), ts)));
       if (++taken == nseq) return p + 1 < x.nrow;
@@ -466,9 +494,11 @@ struct ChunkDecider {
     const float In = nx < x.nrow ? tb.Inx[tt] : 0.f;
     const double sm = tb.sum[tt];
     while (true) {
-      const int ts = __builtin_amdgcn_readlane(nx, p);
+      const int n = __builtin_amdgcn_readlane(nx, p);
+      const int ts = n & (RowTables::kStop - 1);
       if (ts > p + 1) st.join(m - 1, ts - (p + 1), readlane_d(sm, p));
-      if (ts >= x.nrow) break;
+      if (n >= RowTables::kStop) tn = ts;
+      if (n >= x.nrow) break;
       open_at(ts, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(In), p)));
       if (p + 1 >= x.nrow) break;
     }

@@ -93,3 +93,87 @@ def test_float32_precision(dtype, dk, dv, lo, hi):
           flush=True)
     assert err.max() < 1.1e-6
     assert worst < 8e-7
+
+
+def _forced(w, x, beta, bo):
+    """Scores and newest states of a prefill with every boundary forced, and the
+    oracle's; the cache is large enough that nothing merges."""
+    import torch
+    from paper_2606_10650_amd import dla
+    xf = H.f64(x, w)
+    ref = oracle_forward(xf["k"], xf["v"], xf["g"], w.C, w.tau, q=xf["q"], lam=xf["lam"],
+                         beta=beta.astype(np.float64), b_override=bo)
+    n = w.B * w.H
+    q, k, v, g, _ = H.inputs_to_device(w, x, w.B, w.H)
+    cache = dla.cache_alloc(w.B, w.H, w.C, w.dk, w.dv, device="cuda")
+    dev = lambda a: torch.from_numpy(a).reshape(w.B, w.H, w.T).cuda()  # noqa: E731
+    out, _, _, s = dla.prefill_delta(cache, q, k, v, g, dev(beta), None, tau=w.tau,
+                                     boundary_override=dev(bo))
+    return s.cpu().numpy().reshape(n, w.T), ref, dla.cache_export(cache)
+
+
+@pytest.mark.parametrize("dtype,dk,dv", [("f32", 128, 128), ("f32", 64, 64), ("bf16", 64, 128)])
+@pytest.mark.parametrize("scale", [0.0, 1e-4, 1e-3, 1e-2, 0.3])
+def test_steps_that_erase_the_state(dtype, dk, dv, scale):
+    """beta = 1 and a repeated key replace a state's value by one `scale` times as
+    large, so that |S|^2 is a small rest of large terms: at a chunk's first and
+    last tokens, across two chunks, against states from before the chunk, from
+    inside it and in a run of boundaries; afterwards ordinary tokens.  A float32
+    state keeps the new value to 2^-24 of the old one, hence the scores."""
+    T, n = 270, 3
+    w = WORKLOADS["cfg2"].replace(B=1, H=n, T=T, C=80, dk=dk, dv=dv, dtype=dtype, mean_len=40.0,
+                                  seed=5)
+    x = make_inputs(w)
+    beta = make_beta(w)
+    rng = np.random.default_rng(3)
+    bo = np.zeros((n, T), np.int8)
+    pairs = [1, 12, 30, 62, 64, 100, 126, 128, 131] + list(range(194, 226, 2))
+    k = to_f64(x["k"], dtype)
+    v = to_f64(x["v"], dtype)
+    for t in pairs + [63, 127]:                                # (63, 64), (127, 128): next chunk
+        bo[:, t] = 1
+        bo[:, t + 1] = 0
+        for h in range(n):
+            e = np.zeros(dk)                                   # |k| = 1 exactly
+            e[rng.choice(dk, 4, replace=False)] = 0.5
+            k[h, t] = k[h, t + 1] = e
+        v[:, t + 1] = scale * rng.standard_normal((n, dv))
+        beta[:, t:t + 2] = 1.0
+    x["k"], x["v"] = store(k, dtype), store(v, dtype)
+    s, ref, exp = _forced(w, x, beta, bo)
+    err = np.abs(s - ref["score"]) / np.maximum(ref["score"], 1.0)
+    tol = 1e-5 + (4.0 * 2.0 ** -24 / scale if scale else 0.0)
+    print(f"[erase] {dtype} {dk}x{dv} {scale}: largest score error {np.nanmax(err):.2e} of {tol:.1e}, "
+          f"{int(np.isnan(s).sum())} NaN", flush=True)
+    assert err.max() < tol
+    S = H.true_states(exp)
+    for h in range(n):
+        m = int(ref["cache"].m[h])
+        assert exp["m"][h] == m and (exp["n"][h, :m] == ref["cache"].n[h, :m]).all()
+        assert np.allclose(exp["ibar"][h, :m], ref["cache"].ibar[h, :m], rtol=tol, atol=tol)
+        Sr = ref["cache"].S[h, m - 1]
+        assert np.linalg.norm(S[h, m - 1] - Sr) < 1e-5 * np.linalg.norm(Sr)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_values_whose_square_overflows(dtype):
+    """Two values of size 1e25 (their squares are past float32) in a chunk: no
+    token before them, and no state that begins after them, changes."""
+    T, n = 200, 2
+    w = WORKLOADS["cfg2"].replace(B=1, H=n, T=T, C=40, dk=64, dv=64, dtype=dtype, mean_len=20.0,
+                                  seed=8)
+    x = make_inputs(w)
+    beta = make_beta(w)
+    bo = np.zeros((n, T), np.int8)
+    bo[:, [20, 90, 110, 150]] = 1
+    v = to_f64(x["v"], dtype)
+    v[:, 100:102] *= 1e25
+    x["v"] = store(v, dtype)
+    s, ref, exp = _forced(w, x, beta, bo)
+    ok = np.r_[0:100, 111:T]
+    assert np.abs(s - ref["score"])[:, ok].max() < 1e-5
+    S = H.true_states(exp)
+    for h in range(n):
+        m = int(ref["cache"].m[h])
+        Sr = ref["cache"].S[h, m - 1]
+        assert np.linalg.norm(S[h, m - 1] - Sr) < 1e-5 * np.linalg.norm(Sr)
