@@ -92,7 +92,7 @@ struct DeltaP {
     off += (size_t)SL * 8 * 4;            // sG, sAl2, sKK, sV2
     off += (size_t)SL * 4 * 5;            // float rows, boundary overrides
     off += 64 + 128;                      // sRed, sMisc
-    if (C > kMaxRegC) off += (size_t)C * (8 + 4 + 4);
+    if (C > 64) off += (size_t)C * (8 + 4 + 4);
     return round_up(off, 16);
   }
 };
@@ -977,8 +977,10 @@ static hipError_t launch_delta_scan_t(const PrefillArgs& a, const PrefillWS& w, 
     hipLaunchKernelGGL(k, dim3(a.desc.B * a.desc.H), dim3(STHR), shm, s, a, w, tb, te, beta, U, U16);
     return hipGetLastError();
   };
-  if (a.desc.C > kMaxRegC) return launch(prefill_delta_scan_kernel<DK, DV, Tin, 0>);
-  if (a.desc.C > 64) return launch(prefill_delta_scan_kernel<DK, DV, Tin, 4>);
+  // (Four registers per lane and field for C up to 256, as in the gated scan,
+  // spill 50 to 120 of this kernel's: 48 float32 heads of 128 x 128, 2048 tokens, C =
+  // 128 took 2238 us, with the states in LDS 1374 without the readout.)
+  if (a.desc.C > 64) return launch(prefill_delta_scan_kernel<DK, DV, Tin, 0>);
   return launch(prefill_delta_scan_kernel<DK, DV, Tin, 1>);
 }
 
