@@ -1049,7 +1049,23 @@ hipError_t launch_prefill_delta(const PrefillArgs& a, const float* beta, hipStre
   fr.v_f32 = 0;
   if (wide) fr.v = U16;
   const bool pipe = pipelined(a.T, a.in_dtype, readout, serial);
-  const SegPlan p = seg_plan(a.desc, a.T, a.in_dtype, readout, serial, a.pool_budget);
+  SegPlan p = seg_plan(a.desc, a.T, a.in_dtype, readout, serial, a.pool_budget);
+  if (pipe && p.shared) {
+    // The scan is the long stage where heads are few, inputs are float32 or chunks
+    // go token by token, so the segments stay at the ramp's first size instead of
+    // growing: what remains after the scan, the last segment's update and readout,
+    // is then short (48 heads of 128 x 128, 2048 tokens: float32 2456 -> 2265 us,
+    // bfloat16 1306 -> 1225, token by token 4226 -> 3446 and 3356 -> 3225).  The
+    // pool is shared, so the segments change neither the workspace nor the results.
+    p.fit = p.first;
+    p.nseg = 0;
+    p.nch_seg = 0;
+    for (int b = 0; b < p.nch; ++p.nseg) {
+      const int n = ramp_size(p.first, p.fit, p.nseg, p.nch - b);
+      p.nch_seg = n > p.nch_seg ? n : p.nch_seg;
+      b += n;
+    }
+  }
   const PrefillWS w = ws_layout(base, nh, a.T, a.desc.C, a.desc.d_k * a.desc.d_v, p.nch);
   hipError_t e;
   if ((e = launch_prefill_prep(fu, s)) != hipSuccess) return e;
