@@ -36,12 +36,12 @@
 // (beta near 2: 4e-6, the states 3e-6), now by 4e-7 and the states by 2e-7
 // (5e-7, 6e-7); 8 x 16 heads x 4k tokens took 2.96 ms, now 3.30.
 //
-// Bound: latency, as the gated scan: a chain of eight phases between barriers,
-// about 20 us a chunk at d = 128 (128 heads x 4096 tokens: 1.3 ms).  Taking the
-// tokens one by one, as chunks with non-finite inputs or expanding steps still
-// are, costs two barriers and a reduction per token, 1.2 us, and made the scan
-// the whole call: 8 x 16 heads x 4k tokens 6.64 ms, now 2.35 ms; 12 heads x
-// 1,100 tokens 1.41 ms, now 0.44 ms.
+// Bound: latency, as the gated scan: a chain of phases between barriers, 33 us a
+// chunk at d = 128 with a state per 30 tokens (48 heads x 2048 tokens: 1.05 ms
+// without the readout).  Taking the tokens one by one, as chunks with non-finite
+// inputs, expanding steps or erased states still are, costs one barrier, a
+// reduction and a score per token, 1.5 us (48 heads x 2048 tokens 3.12 ms; 3.77
+// with two full barriers and the norms of k and v formed per token).
 //
 // The call then runs the chunked update and readout stages of the gated form
 // over (q, k, u, lambda), on the gated prefill's schedule: with the scan in
@@ -134,6 +134,14 @@ __device__ __forceinline__ double exp_gate(double x) {
   return __builtin_ldexp(p, (int)n);
 }
 
+// A workgroup barrier that orders LDS accesses only: stores to global memory stay
+// in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // NR: see the gated scan.
 template <int DK, int DV, typename Tin, int NR>
 __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a, PrefillWS w,
@@ -197,8 +205,8 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
   int32_t* sBo = reinterpret_cast<int32_t*>(sBeta + SL);  // boundary overrides
   int32_t* sMisc = sBo + SL;
   // sMisc: 0, 1 boundary mask; 2 start of the rows left (-1: none); 3 go on with
-  // the row tables; 4, 5 non-finite inputs of an even, an odd chunk; 6 the
-  // decision of the token by token path; 7 tokens that the rows decided
+  // the row tables; 4, 5 non-finite inputs of an even, an odd chunk; 6 tokens that
+  // the rows decided
   __shared__ double sGlast[1];
 
   Meta M = meta_at(a.cache + a.meta_offset + (size_t)h * a.meta_stride, C);
@@ -305,6 +313,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     }
   };
   prefetch(tb);
+  int hold = 0, wait = 0;  // chunks to go token by token
   double Gprev = tb > 0 ? Gtok[tb - 1] : G0;
 
   for (int c0 = tb; c0 < te; c0 += SL) {
@@ -373,7 +382,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
 #pragma unroll
     for (int i = 0; i < SWAVE; ++i) kk += sPq[i * SL + lane];
     const float bk = sBeta[lane] * kk;
-    const bool serial =  // (workgroup-uniform)
+    const bool outside =  // (workgroup-uniform)
         *sBad != 0 || is_bad((float)b0) || __ballot(!(bk >= 0.f && bk <= 2.f)) != 0;
     if (tid == 0) sMisc[4 + (((c0 / SL) & 1) ^ 1)] = 0;
     const int mforce = mpre;  // merge override of the lane's token (wave 0)
@@ -394,7 +403,14 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
       dec.io = 0.f;
     }
 
+    // After a chunk that lost a token the next ones go token by token from their
+    // start, without the tables: 1, then 3 chunks, then 7.  (Counted anew at every
+    // readout chunk, so that results do not depend on the call's segments.)
+    if (c0 % chunk_len(P::E) == 0) hold = wait = 0;
+    const bool waits = wait > 0;
+    if (waits) --wait;
     int tn = 0;  // tokens taken together; the others follow one by one
+    const bool serial = outside || waits;  // (workgroup-uniform)
     bool together = !serial;
     f32x4 X[4];   // X[i][r]: token 16 i + 4 q4 + r, column col
     f32x4 Vr[4];  // the values in the same layout
@@ -670,7 +686,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           sMisc[0] = (int)(uint32_t)dec.B;
           sMisc[1] = (int)(uint32_t)(dec.B >> 32);
           sMisc[2] = more ? dec.p : -1;
-          sMisc[7] = dec.tn;
+          sMisc[6] = dec.tn;
         }
       }
       __syncthreads();
@@ -741,7 +757,7 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         if (wv == 0 && lane == 0) {
           sMisc[0] = (int)(uint32_t)dec.B;
           sMisc[1] = (int)(uint32_t)(dec.B >> 32);
-          sMisc[7] = dec.tn;
+          sMisc[6] = dec.tn;
         }
         __syncthreads();
       }
@@ -755,7 +771,9 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         return x ? 63 - __clzll((long long)x) : -1;
       };
       const int plast = start_of(SL - 1);
-      tn = __builtin_amdgcn_readfirstlane(sMisc[7]);
+      tn = __builtin_amdgcn_readfirstlane(sMisc[6]);
+      hold = tn < nrow ? 2 * hold + 1 : 0;
+      wait = hold;
       if (tn > 0 && tn < nrow) {  // (workgroup-uniform) decays to the last of the tokens taken
         if (tid < SL) sDe[tid] = tid < tn ? (float)exp_gate(sG[tn - 1] - sG[tid]) : 0.f;
         __syncthreads();
@@ -856,11 +874,32 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
     if (tn < nrow) {
       fresh_lane();
       // ---------------------------------------------------- token by token
+      // One barrier per token, for LDS only (the pseudo-values' stores stay in
+      // flight): every wave that holds state columns adds the waves' shares of
+      // |S|^2 and y . v and takes the decision itself, wave 0 keeps the books.
+      if (serial) {  // (else the Gram products left them)
+        for (int t = wv; t < nrow; t += SWAVE) {
+          float kk2 = 0.f, vv2 = 0.f;
+          for (int i = lane; i < DK; i += 64) kk2 += to_f32(sK[t * KRS + i]) * to_f32(sK[t * KRS + i]);
+          for (int i = lane; i < DV; i += 64) vv2 += to_f32(sV[t * VRS + i]) * to_f32(sV[t * VRS + i]);
+          kk2 = wave_total_dpp(kk2);
+          vv2 = wave_total_dpp(vv2);
+          if (lane == 0) {
+            sKK[t] = (double)kk2;
+            sV2[t] = (double)vv2;
+          }
+        }
+        lds_barrier();
+      }
       for (int t = tn; t < nrow; ++t) {
-        float y = 0.f, b = 0.f, kr[NI][4];
+        // shares of |S|^2, y . v: two sets in turn, so that the next token's need
+        // not wait for this one's readers
+        float2* sh = reinterpret_cast<float2*>(sPc) + (t & 1) * SWAVE;
+        float y = 0.f, kr[NI][4];
         const float vt = own ? to_f32(sV[t * VRS + col]) : 0.f;
         if (own) {
           const float al = sAl[t];
+          float b = 0.f;
 #pragma unroll
           for (int i = 0; i < NI; ++i) {
             load4f(sK + t * KRS + 16 * i + 4 * q4, kr[i]);
@@ -871,48 +910,31 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
               b += S[i][r] * S[i][r];
             }
           }
+          b = wave_total_dpp(b);
+          const float c = wave_total_dpp(y * vt);
+          if (lane == 0) sh[wv] = make_float2(b, c);
           y += __shfl_xor(y, 16, 64);
           y += __shfl_xor(y, 32, 64);
-          b = wave_total_dpp(b);
-          const float c = wave_total_dpp(q4 == 0 ? y * vt : 0.f);
-          if (lane == 0) {
-            sPc[wv] = b;  // (sPq may still be read for the choice of this path)
-            sPc[16 + wv] = c;
-          }
         }
-        __syncthreads();
-        if (wv == 0) {
-          float kk2 = 0.f, vv2 = 0.f;
-          for (int i = lane; i < DK; i += 64) kk2 += to_f32(sK[t * KRS + i]) * to_f32(sK[t * KRS + i]);
-          for (int i = lane; i < DV; i += 64) vv2 += to_f32(sV[t * VRS + i]) * to_f32(sV[t * VRS + i]);
-          kk2 = wave_sum(kk2);
-          vv2 = wave_sum(vv2);
+        lds_barrier();
+        if (own) {
           double bs = 0.0, cs = 0.0;
 #pragma unroll
           for (int i = 0; i < NW; ++i) {
-            bs += (double)sPc[i];
-            cs += (double)sPc[16 + i];
+            const float2 x = sh[i];
+            bs += (double)x.x;
+            cs += (double)x.y;
           }
           int bd = 1;
           float It = 0.f;  // the first token of an empty cache opens a state with score 0
-          if (dec.m > 0) {
-            It = score_f(kk2 * vv2, (float)bs, (float)cs, (float)D, a.eps, a.eps_rms);
+          if (m0 > 0 || c0 + t > 0) {
+            It = score_f((float)sKK[t] * (float)sV2[t], (float)bs, (float)cs, (float)D, a.eps,
+                         a.eps_rms);
             bd = (It >= a.tau) ? 1 : 0;
             if (sBo[t] != -1) bd = sBo[t] ? 1 : 0;
             if (C == 1) bd = 0;
           }
           bd = __builtin_amdgcn_readfirstlane(bd);
-          if (bd) {
-            open_at(t, It);
-          } else {
-            dec.st.join(dec.m - 1, 1, (double)It);
-            if (lane == t) dec.io = It;
-          }
-          if (lane == 0) sMisc[6] = bd;
-        }
-        __syncthreads();
-        if (own) {
-          const bool bd = sMisc[6] != 0;
           const float u = sBeta[t] * (vt - (bd ? 0.f : y));
           if (q4 == 0) {
             Uh[(size_t)(c0 + t) * DV + col] = u;
@@ -922,6 +944,14 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int r = 0; r < 4; ++r) S[i][r] = (bd ? 0.f : S[i][r]) + kr[i][r] * u;
+          if (wv == 0) {
+            if (bd) {
+              open_at(t, It);
+            } else {
+              dec.st.join(dec.m - 1, 1, (double)It);
+              if (lane == t) dec.io = It;
+            }
+          }
         }
       }
     }

@@ -177,3 +177,36 @@ def test_values_whose_square_overflows(dtype):
         m = int(ref["cache"].m[h])
         Sr = ref["cache"].S[h, m - 1]
         assert np.linalg.norm(S[h, m - 1] - Sr) < 1e-5 * np.linalg.norm(Sr)
+
+
+@pytest.mark.parametrize("dtype,T", [("bf16", 2600), ("f32", 1100)])
+def test_token_by_token_chunks_pipelined_matches_serial(dtype, T):
+    """Chunks that go token by token from the start, from a token that erases the
+    state, or because the chunk before had one: the pipelined call, whose scan
+    runs in segments, equals the serial one bit for bit."""
+    import torch
+    from paper_2606_10650_amd import dla
+    n = 3
+    w = WORKLOADS["cfg2"].replace(B=1, H=n, T=T, C=90, dk=64, dv=128, dtype=dtype, mean_len=40.0,
+                                  seed=21)
+    x = make_inputs(w)
+    beta = make_beta(w)
+    k, v = to_f64(x["k"], dtype), to_f64(x["v"], dtype)
+    for t in list(range(70, T - 1, 97)) + list(range(T // 2, T // 2 + 300, 2)):
+        k[:, t + 1] = k[:, t]
+        v[:, t + 1] *= 0.01
+        beta[:, t:t + 2] = 1.0
+    k[:, 900] *= 1.7                              # beta |k|^2 > 2
+    beta[:, 900] = 1.0
+    x["k"], x["v"] = store(k, dtype), store(v, dtype)
+    q, kd, vd, g, lam = H.inputs_to_device(w, x, 1, n)
+    bt = torch.from_numpy(beta).reshape(1, n, T).cuda()
+    got = []
+    for serial in (False, True):
+        cache = dla.cache_alloc(1, n, w.C, w.dk, w.dv, device="cuda")
+        r = dla.prefill_delta(cache, q, kd, vd, g, bt, lam, tau=w.tau, serial=serial)
+        got.append([a.view(torch.int16) if a.dtype == torch.bfloat16 else a for a in r] +
+                   [torch.from_numpy(np.ascontiguousarray(a)) for a in dla.cache_export(cache).values()
+                    if isinstance(a, np.ndarray)])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
