@@ -393,8 +393,9 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
       dec.open(ts, Is, mforce, c0, C, T, &reinterpret_cast<CacheHeader*>(a.cache)->flags,
                [&](int ld, int tk) { (ld >= 0 ? death[ld] : iv.death0[ld + m0]) = tk; });
     };
-    const bool dense = __popcll(dec.B) >= NSEQ;  // (wave 0)
+    bool dense = false;
     if (wv == 0) {
+      dense = dec.dense();
       dec.p = -1;
       dec.tn = nrow;
       dec.B = 0;

@@ -23,7 +23,8 @@
 // The score (rank-one closed form of the RMS-normalised distance, Sec. 3.1)
 // and the boundary test then hold for every token of a row at once; a ballot
 // finds the first boundary, which starts the next row.  Each boundary runs the
-// capacity schedule of Alg. 2 on the (count, score) pairs in LDS.  At the
+// capacity schedule of Alg. 2 on the (count, score) pairs, held by wave 0 in
+// registers or, for large capacities, in LDS.  At the
 // chunk end the newest state (float32 MFMA accumulators, 32 x 32 tiles spread
 // over the waves) is advanced by the chunk's tokens.  Emits b_t, merge index and
 // score per token, and the death token of every state leader (the token at
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(STHR) void prefill_scan_kernel(PrefillArgs a, Prefi
                [&](int ld, int tk) { (ld >= 0 ? death[ld] : iv.death0[ld + m0]) = tk; });
     };
     if (wv == 0) {
-      const int nseq = __popcll(dec.B) >= NSEQ ? 1 : NSEQ;
+      const int nseq = dec.dense() ? 1 : NSEQ;
       dec.p = -1;
       dec.tn = nrow;  // (no token is lost in the gated form)
       dec.B = 0;

@@ -7,9 +7,13 @@
 // of about 2.5 k cycles (an affine scan over the lanes and the score's
 // divisions), so where boundaries are dense all eight waves evaluate the rows
 // of every start still possible at once, and what is left per boundary is a
-// lookup and the capacity schedule, in registers.  That costs a chunk about as
-// much as three rows; it is taken from the NSEQ-th boundary of a chunk on, and
-// from the first when the chunk before had that many.
+// lookup and the capacity schedule.  That costs a chunk about as much as three
+// rows; it is taken from the NSEQ-th boundary of a chunk on, and from the first
+// when the two chunks before had that many.  (With four instead of eight, and one
+// chunk before, prompts of two to four independent boundaries per chunk paid for
+// both: 48 heads of 64 x 128, 4.4k tokens, a state per 18 / 24 / 32 tokens 1684 /
+// 1359 / 1233 us, now 1582 / 1276 / 1178; row by row alone 1580 / 1272 / 1180, but
+// a state per token, 1k tokens, 964 us instead of 658.)
 #pragma once
 #include "mfma.h"
 #include "prefill.h"
@@ -19,7 +23,7 @@ namespace dla {
 constexpr int SL = 64;      // tokens per scan chunk (one per lane of a wavefront)
 constexpr int SWAVE = 8;    // waves per scan workgroup
 constexpr int STHR = 64 * SWAVE;
-constexpr int NSEQ = 4;     // boundaries of a chunk taken row by row
+constexpr int NSEQ = 8;     // boundaries of a chunk taken row by row
 
 // Transposed copy of a 16-bit piece (columns 8 pc .. 8 pc + 7 of token r, r =
 // lane): the lane pair (2i, 2i + 1) swaps halves, so each lane writes 32-bit
@@ -175,7 +179,7 @@ struct StatesInRegs {
 // NR = 1, since the scan has few registers left (four more of each spill).
 constexpr int kMaxRegC = 256;
 
-// The same in LDS, for capacities past kMaxRegC.
+// The same in LDS, for larger capacities.
 struct StatesInLds {
   double* I;
   int32_t *n, *ld;
@@ -412,8 +416,15 @@ struct ChunkDecider {
   // one whose step leaves the lost |S|^2
   int tn;
   uint64_t B;
+  int runs = 0;  // chunks in a row with NSEQ boundaries or more
   int mo, dc;
   float io;
+
+  // whether the chunk to come is taken by the row tables from its first boundary
+  __device__ __forceinline__ bool dense() {  // (B: the chunk before)
+    runs = __popcll(B) >= NSEQ ? runs + 1 : 0;
+    return runs >= 2;
+  }
 
   // a state opens at token ts of the chunk with score Is: Alg. 2 when the cache
   // is full, then the new state.  kill(lead, token) records the death of a state

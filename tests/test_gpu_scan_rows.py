@@ -67,6 +67,36 @@ def test_dense_runs(form, dtype, dk, dv, C):
     H.assert_cache(exp, ref["cache"], H.STATE_TOL[False])
 
 
+@pytest.mark.parametrize("C", [64, 65, 200])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_dense_runs_of_the_largest_states(dtype, C):
+    """128 x 128 states, whose bookkeeping leaves the registers past 64 states."""
+    test_dense_runs("gated", dtype, 128, 128, C)
+
+
+@pytest.mark.parametrize("form", ["gated", "delta"])
+def test_long_runs_of_boundaries(form):
+    """Runs of dense chunks, which from the third on go by the row tables at once,
+    between chunks with 7, 8 and 9 boundaries on either side of the tables' first
+    use, and sparse ones."""
+    T, C = 64 * 14 + 5, 33
+    w = WORKLOADS["cfg2"].replace(B=1, H=2, T=T, C=C, dk=64, dv=64, mean_len=30.0, seed=77)
+    x = make_inputs(w)
+    bo = np.zeros((2, T), np.int8)
+    mo = np.full((2, T), -1, np.int32)
+    for chunk, step in enumerate((9, 8, 7, 1, 2, 1, 3, 64, 7, 8, 1, 1, 64, 1)):
+        bo[:, 64 * chunk:64 * chunk + 64:step] = 1
+    mo[:, ::5] = np.random.default_rng(1).integers(0, C - 1, size=mo[:, ::5].shape)
+    beta = make_beta(w) if form == "delta" else None
+    ref = _oracle(w, x, beta, bo, mo)
+    bo2, mo2, _, _ = H.near_tie_overrides(ref, bo, mo, f"long runs {form}", max_frac=0.02)
+    out, b, m, s, exp = _run(w, x, beta, bo2, mo2)
+    H.assert_decisions(b, m, ref)
+    assert np.abs(s - ref["score"]).max() < 1e-5
+    H.assert_outputs(out, ref["out"], H.TOL["bf16"])
+    H.assert_cache(exp, ref["cache"], H.STATE_TOL[False])
+
+
 @pytest.mark.parametrize("dtype,dk,dv", [("bf16", 128, 128), ("f32", 64, 64), ("bf16", 128, 64)])
 @pytest.mark.parametrize("where", ["k", "v", "beta"])
 @pytest.mark.parametrize("t0", [0, 63, 64, 100, 210])
