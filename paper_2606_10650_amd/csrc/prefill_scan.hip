@@ -134,7 +134,7 @@ struct ScanP {
     off += (size_t)SWAVE * SL * 4;                      // sPart
     off += (size_t)SL * 4 * 8;                          // float rows, int rows
     off += 64;                                          // sMisc
-    if (C > kMaxRegC) off += (size_t)C * (8 + 4 + 4);
+    if (C > max_reg_c(DK, DV)) off += (size_t)C * (8 + 4 + 4);
     return round_up(off, 16);
   }
 };
@@ -657,8 +657,9 @@ static hipError_t launch_scan_t(const PrefillArgs& a, const PrefillWS& w, int nh
     hipLaunchKernelGGL(k, dim3(nh), dim3(STHR), shm, s, a, w, tb, te);
     return hipGetLastError();
   };
-  if (a.desc.C > kMaxRegC) return launch(prefill_scan_kernel<DK, DV, Tin, 0>);
-  if (a.desc.C > 64) return launch(prefill_scan_kernel<DK, DV, Tin, 4>);
+  if (a.desc.C > max_reg_c(DK, DV)) return launch(prefill_scan_kernel<DK, DV, Tin, 0>);
+  if constexpr (max_reg_c(DK, DV) > 64)
+    if (a.desc.C > 64) return launch(prefill_scan_kernel<DK, DV, Tin, 4>);
   return launch(prefill_scan_kernel<DK, DV, Tin, 1>);
 }
 

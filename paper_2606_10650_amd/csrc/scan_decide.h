@@ -175,9 +175,12 @@ struct StatesInRegs {
   }
 };
 
-// Largest capacity whose bookkeeping stays in registers (NR = 4); C <= 64 takes
-// NR = 1, since the scan has few registers left (four more of each spill).
-constexpr int kMaxRegC = 256;
+// Largest capacity whose bookkeeping stays in registers in a scan of d_k x d_v
+// states: 64 (NR = 1) at 128 x 128, where NR = 4 spills 19 registers and the LDS
+// form none (48 heads, 4k tokens, 200 / 100 states: NR = 4 1312 / 1017 us, LDS 1290 /
+// 986; 4 x 16 heads x 16k tokens, 128 states, 5032 and 4974); else 256 (NR = 4; 48
+// heads of 64 x 128, 4.4k tokens, 256 states: NR = 4 1582 us, LDS 1625).
+constexpr int max_reg_c(int dk, int dv) { return dk * dv >= 128 * 128 ? 64 : 256; }
 
 // The same in LDS, for larger capacities.
 struct StatesInLds {
