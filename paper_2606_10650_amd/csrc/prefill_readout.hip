@@ -182,6 +182,8 @@ __global__ __launch_bounds__(RTHR) void prefill_readout_kernel(PrefillArgs a, Pr
   const int c0 = c * RL;
   const int nrow = min(RL, T - c0);
   const int nblk = (nrow + 31) >> 5;
+  // a part whose tiles all lie past the chunk's tokens
+  if (PARTS > 1 && 32 * tile_of<NT>(part * (RWAVE / PARTS), 0) >= nrow) return;
 
   // whether the wave serves its tiles (their first is the earliest) here; else it
   // only helps to load.  (With one part every wave takes the same path: a
@@ -800,10 +802,11 @@ static hipError_t launch_readout_t(const PrefillArgs& a, const SegPlan& p, int s
   };
   // Two parts where both fit on the chip at once, beside the scan of the next
   // segments (one workgroup per compute unit each): a second round would cost
-  // what the halves save.  15 float32 heads of 64 x 64, 1531 tokens in two
-  // calls and a decode step: 616 -> 526 us.
+  // what the halves save.  And where the second part has tiles, from the 129th
+  // token of a chunk on.  15 float32 heads of 64 x 64, 1531 tokens in two calls and
+  // a decode step: 616 -> 526 us.
   const bool scanning = seg + 1 < p.nseg && pipelined(a.T, a.in_dtype, true, a.serial != 0);
-  const bool two = 2 * grid1 + (scanning ? nh : 0) <= 256;
+  const bool two = 2 * grid1 + (scanning ? nh : 0) <= 256 && a.T - cs * p.RL > 32 * RWAVE / 2;
   if (a.out_dtype == DLA_F32)
     return two ? launch(prefill_readout_kernel<DK, DV, Tin, float, 2>, 2)
                : launch(prefill_readout_kernel<DK, DV, Tin, float, 1>, 1);
