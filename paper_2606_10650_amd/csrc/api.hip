@@ -365,7 +365,8 @@ static dla_status decode_impl(const dla_cache_desc* desc, void* cache, const voi
   a.meta_stride = L.meta_stride;
   a.states_offset = L.states_offset;
   a.open_offset = L.open_offset;
-  a.nsplit = decode_splits(desc->B * desc->H, desc->C, desc->d_k * desc->d_v);
+  a.nsplit = decode_splits(desc->B * desc->H, desc->C, desc->d_k * desc->d_v,
+                           (int)state_elem_bytes(*desc));
   a.q = q;
   a.k = k;
   a.v = v;

@@ -33,7 +33,8 @@ struct DecodeArgs {
 
 hipError_t launch_decode(const DecodeArgs& a, int nheads, int dk, int dv, dla_dtype in,
                          dla_dtype out, hipStream_t s);
-// workgroups per head for nheads heads of capacity C, states of D elements
-int decode_splits(int nheads, int C, int D);
+// workgroups per head for nheads heads of capacity C, states of D elements of
+// state_bytes bytes
+int decode_splits(int nheads, int C, int D, int state_bytes);
 
 }  // namespace dla

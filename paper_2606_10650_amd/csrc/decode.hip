@@ -661,27 +661,52 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(DecodeArgs a) {
                                 [&](int r) { return ld_group<true>(newest, threadIdx.x + 256 * r); });
 }
 
-// Workgroups per head.  With the next state always in flight one workgroup per
-// compute unit keeps memory busy (two where a state has less than 8192
-// elements), and a second one only repeats the decisions: 32 heads of 128
-// float32 states, 128 x 128, take 56.6 / 58.2 us a step split by 5 / 8 (at most
-// 256 workgroups), 74.3 / 64.5 us by 9 / 16.  So the split is the one whose
-// rounds over the chip, each a workgroup's states and its decisions (worth
-// about 15 states), are shortest; at most kMaxSplit, and at least two states
-// per workgroup.  Heads beyond the chip: 384 of 30 states, 128 x 64, 73.7 us
-// unsplit, 75.7 / 80.1 by 2 / 3; 384 of 128 bfloat16 states 160 us unsplit, 147
-// by 2; 640 of 100 states, 128 x 128, 711 us unsplit, 636 by 2.  From four
-// rounds on the rounds' rest no longer counts and the unsplit step, without a
-// second kernel, is taken.
-int decode_splits(int nheads, int C, int D) {
-  constexpr int kDecide = 15;
+// Workgroups per head: the split of the shortest estimated step, at most kMaxSplit
+// and at least two states per workgroup.  Estimate (us): rounds of the workgroups
+// that the chip holds at once (by the kernels' registers).  A round takes its
+// decisions and then the longer of one workgroup's chain of loads, state after
+// state, and the round's share of memory (1.9 for a 64 KiB state per compute unit,
+// and the newest state).  A split workgroup has the next state in flight, which
+// shortens its chain, but repeats the decisions, and a second kernel ends the step.
+// So small states (bfloat16, 64 x 64), bound by the chain, want the split where
+// 64 KiB ones, bound by memory, do not.
+//
+// Fitted to 792 shapes (4 to 1016 heads, 8 to 256 states, all sizes and types; steps
+// over several caches in turn, so that no state is on chip): 1.4% over the best
+// split on average, 15% at most beside any rule tried.  us, unsplit / split in 2:
+//   512 heads of 128 bfloat16 states, 64 x 64          175 / 102
+//   256 heads of 128 bfloat16 states, 128 x 64         134 /  95
+//   768 heads of 128 bfloat16 states, 128 x 128        576 / 507
+//   384 heads of  30 float32  states, 128 x 64          68 /  78
+//    32 heads of 128 float32  states, 128 x 128        156 /  96; in 5: 59, 8: 60, 16: 65
+// From 1024 heads on the unsplit step fills the chip: 1200 heads of 64 states,
+// 64 x 64, float32 210 / 211, bfloat16 117 / 121.
+int decode_splits(int nheads, int C, int D, int state_bytes) {
   if (nheads >= 1024) return 1;
-  const int slots = D >= 8192 ? 256 : 512;
+  const bool wide = state_bytes == 4;
+  // workgroups that a compute unit holds, unsplit and split
+  const int held1 = D >= 16384 ? 2 : (D >= 8192 ? 3 : 6);
+  const int held2 = D >= 16384 ? (wide ? 1 : 2) : (D >= 8192 ? (wide ? 3 : 4) : (wide ? 5 : 6));
+  const float d = (float)D / 16384.f;                     // elements, of a 128 x 128 state
+  const float mem = 1.9f * d * (float)state_bytes / 4.f;  // one state per compute unit
   const int most = C / 2 < kMaxSplit ? C / 2 : kMaxSplit;
-  int best = 1, cost = 0;
+  int best = 1;
+  float cost = 0.f;
   for (int ns = 1; ns <= most; ++ns) {
-    const int c = (nheads * ns + slots - 1) / slots * (kDecide + (C + ns - 1) / ns);
-    if (ns == 1 || c < cost) {
+    const bool split = ns > 1;
+    const int held = split ? held2 : held1;
+    const float chain = split ? 0.55f + 0.3f * d : 0.8f + 0.6f * d;  // a state's loads
+    const float n = (float)((C + ns - 1) / ns);
+    auto round = [&](int wgs) {  // of wgs workgroups
+      // (the busiest unit's share of memory, and the average one's)
+      const float k = 0.4f * (float)((wgs + 255) / 256) + 0.6f * (float)wgs / 256.f;
+      const float a = n * chain, b = k * (n * mem + (split ? 4.5f : 5.f) * d);
+      return (split ? 3.f : 5.f) + (a > b ? a : b);
+    };
+    const int wgs = nheads * ns, slots = 256 * held;
+    const int full = wgs / slots, rest = wgs % slots;
+    const float c = (split ? 8.f : 0.f) + (float)full * round(slots) + (rest ? round(rest) : 0.f);
+    if (!split || c < cost) {
       cost = c;
       best = ns;
     }
