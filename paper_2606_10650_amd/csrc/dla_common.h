@@ -224,21 +224,18 @@ __device__ __forceinline__ float wave_total_dpp(float x) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
-// Sums of a double over the wavefront.
+// Sum of a double over the wavefront (every lane gets it).
 template <int CTRL, int RMASK>
 __device__ __forceinline__ void sum_step_d(double& x) {
   x += dpp_d<CTRL, RMASK>(0.0, x);
 }
-__device__ __forceinline__ void wave_prefix_d(double& x) {  // inclusive, over the lanes
+__device__ __forceinline__ double wave_sum_d(double x) {
   sum_step_d<0x111, 0xF>(x);
   sum_step_d<0x112, 0xF>(x);
   sum_step_d<0x114, 0xF>(x);
   sum_step_d<0x118, 0xF>(x);
   sum_step_d<0x142, 0xA>(x);
   sum_step_d<0x143, 0xC>(x);
-}
-__device__ __forceinline__ double wave_sum_d(double x) {
-  wave_prefix_d(x);
   return readlane_d(x, 63);
 }
 

@@ -82,7 +82,7 @@ struct DeltaP {
   // sV, dead once the Gram products and the carry are formed; then sQ
   static constexpr size_t V_BYTES = cmax((size_t)SL * VRS * E, (size_t)SL * RRS * 4);
   static constexpr size_t T_BYTES = TRANS ? (size_t)(DK + DV) * TRS * E : 0;
-  static_assert(MAT >= (size_t)SL * RRS * 4 && MAT >= RowTables::BYTES, "aliases of sM and sVV");
+  static_assert(MAT >= (size_t)SL * RRS * 4 + SWAVE * SL * 8 && MAT >= RowTables::BYTES, "aliases of sM and sVV");
   static_assert(K_BYTES % 16 == 0 && V_BYTES % 16 == 0 && T_BYTES % 16 == 0 && MAT % 16 == 0,
                 "alignment");
   static size_t smem_bytes(int C) {
@@ -360,8 +360,6 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
       sG[t] = gd;
       sA[t] = (float)exp_gate(gd);
       sAl[t] = (t < nrow) ? __expf(fpre) : 0.f;
-      sAl2[t] = (t < nrow) ? exp_gate(2.0 * (double)fpre) : 0.0;
-      sDe[t] = (t < nrow) ? (float)exp_gate(Glast - gpre) : 0.f;
       sBeta[t] = be;
       sBo[t] = bpre;
       // (a positive gate expands the state: token by token too)
@@ -519,6 +517,10 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           Wb[t * MRS + c16] = wt;
           bw[t] = (double)be[t] * wt;
         }
+      } else if (wv == 1) {  // (beside it)
+        sAl2[lane] = lane < nrow ? exp_gate(2.0 * (sG[lane] - (lane ? sG[lane - 1] : 0.0))) : 0.0;
+      } else if (wv == 2) {
+        sDe[lane] = lane < nrow ? (float)exp_gate(sG[nrow - 1] - sG[lane]) : 0.f;
       }
       __syncthreads();
       fresh_lane();
@@ -554,23 +556,31 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         put4(I, J, pq - wq);
       }
       __syncthreads();
-      if (wv < 2) {  // 32 x 32 blocks: wave tj takes columns 16 tj ..
-        const int tj = wv;
-        f64x4 p0 = zero4, p1 = zero4;
-        for (int kb = tj; kb < 2; ++kb) {
-          const f64x4 b = beta4(kb) * tile4(sW, kb, tj);
-          mma16(p0, row4(sM, 2, kb), b);
-          mma16(p1, row4(sM, 3, kb), b);
+      // the 32 x 32 blocks: wave 2 ti + tj takes rows 16 (2 + ti) .. and columns 16
+      // tj .., the halves' P through the bytes of sPc and sPq
+      double* sP0 = reinterpret_cast<double*>(sPc);
+      f64x4 pw = zero4;
+      if (wv < 4) {
+        const int tj = wv & 1, ti = 2 + (wv >> 1);
+        for (int kb = tj; kb < 2; ++kb) mma16(pw, row4(sM, ti, kb), beta4(kb) * tile4(sW, kb, tj));
+        pw = tile4(sM, ti, tj) - pw;
+        if (ti == 2) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sP0[tj * 256 + (4 * r + q4) * 16 + c16] = pw[r];
         }
-        p0 = tile4(sM, 2, tj) - p0;
-        p1 = tile4(sM, 3, tj) - p1;
-        f64x4 w0 = zero4, w1 = zero4;
-        const f64x4 b0p = beta4(2) * p0;
-        mma16(w0, row4(sW, 2, 2), b0p);
-        mma16(w1, row4(sW, 3, 2), b0p);
-        mma16(w1, row4(sW, 3, 3), beta4(3) * p1);
-        put4(2, tj, p0 - w0);
-        put4(3, tj, p1 - w1);
+      }
+      __syncthreads();
+      if (wv < 4) {
+        const int tj = wv & 1, ti = 2 + (wv >> 1);
+        f64x4 w0 = zero4;
+        if (ti == 3) {
+          f64x4 p0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) p0[r] = sP0[tj * 256 + (4 * r + q4) * 16 + c16];
+          mma16(w0, row4(sW, 3, 2), beta4(2) * p0);
+        }
+        mma16(w0, row4(sW, ti, ti), beta4(ti) * pw);
+        put4(ti, tj, pw - w0);
       }
       __syncthreads();
 
@@ -722,17 +732,35 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
         }
         __syncthreads();
         {
-          const int s = SL - 1 - lane;  // the suffix sum over s is a prefix sum over the lanes
-          const double bs = (double)sBeta[s];
+          // suffix sums over s: lane t, wave w terms 8 w .. 8 w + 7, then the
+          // totals of the waves behind (in the bytes of sPc and past sR)
+          double* sTx = reinterpret_cast<double*>(sPc);
+          double* sTy = sM + SL * RRS / 2;
+          const int t = lane;
+          double x[8], y[8], ax = 0.0, ay = 0.0;
 #pragma unroll
-          for (int t = wv; t < SL; t += SWAVE) {
-            const int at = tile(t >> 4, min(s, t) >> 4) + (t & 15) * MRS + (s & 15);
-            double x = (s < t) ? sW[at] * bs * sVV[at] : 0.0;
-            double y = (s < t) ? (double)sQ[t * RRS + s] : 0.0;
-            wave_prefix_d(x);
-            wave_prefix_d(y);
-            sR[t * RRS + s] = (float)x;
-            sQ[t * RRS + s] = (float)y;
+          for (int j = 7; j >= 0; --j) {
+            const int s = 8 * wv + j;
+            const int at = tile(t >> 4, min(s >> 4, t >> 4)) + (t & 15) * MRS + (s & 15);
+            if (s < t) {
+              ax += sW[at] * (double)sBeta[s] * sVV[at];
+              ay += (double)sQ[t * RRS + s];
+            }
+            x[j] = ax;
+            y[j] = ay;
+          }
+          sTx[wv * SL + t] = ax;
+          sTy[wv * SL + t] = ay;
+          __syncthreads();
+          ax = ay = 0.0;
+          for (int w2 = wv + 1; w2 < SWAVE; ++w2) {
+            ax += sTx[w2 * SL + t];
+            ay += sTy[w2 * SL + t];
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            sR[t * RRS + 8 * wv + j] = (float)(x[j] + ax);
+            sQ[t * RRS + 8 * wv + j] = (float)(y[j] + ay);
           }
         }
         __syncthreads();
