@@ -596,10 +596,10 @@ __global__ __launch_bounds__(STHR) void prefill_delta_scan_kernel(PrefillArgs a,
           const bool in = 2 * kk + j <= i;  // (else above the diagonal)
           const double* wp = sW + (in ? tile(i, 2 * kk + j) : 0) + c16 * MRS + 4 * q4;
           const float4 b = *reinterpret_cast<const float4*>(sBeta + 32 * kk + 16 * j + 4 * q4);
-          x[4 * j] = in ? (float)(wp[0] * (double)b.x) : 0.f;
-          x[4 * j + 1] = in ? (float)(wp[1] * (double)b.y) : 0.f;
-          x[4 * j + 2] = in ? (float)(wp[2] * (double)b.z) : 0.f;
-          x[4 * j + 3] = in ? (float)(wp[3] * (double)b.w) : 0.f;
+          x[4 * j] = in ? (float)wp[0] * b.x : 0.f;
+          x[4 * j + 1] = in ? (float)wp[1] * b.y : 0.f;
+          x[4 * j + 2] = in ? (float)wp[2] * b.z : 0.f;
+          x[4 * j + 3] = in ? (float)wp[3] * b.w : 0.f;
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e)

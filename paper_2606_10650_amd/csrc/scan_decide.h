@@ -277,9 +277,8 @@ template <>
 struct ScoreIn<double> {
   double eps_rms, rD;
   double na, ra;  // a / rs^2, 1 / rs
-  __device__ static __forceinline__ double rsq(double x) {  // two Newton steps
-    double r = __builtin_amdgcn_rsq(x);
-    r = r * (1.5 - 0.5 * x * r * r);
+  __device__ static __forceinline__ double rsq(double x) {  // one Newton step
+    const double r = __builtin_amdgcn_rsq(x);
     return r * (1.5 - 0.5 * x * r * r);
   }
   __device__ static __forceinline__ ScoreIn of(double eps_rms, double D, double a) {
