@@ -34,14 +34,15 @@
 // keys repeat, and |S|^2 is a sum of terms of both signs.  In float32 the scores
 // were off by up to 2e-6 where a float32 token by token scan is off by 5e-7
 // (beta near 2: 4e-6, the states 3e-6), now by 4e-7 and the states by 2e-7
-// (6e-7, 7e-7); a chunk of 48 heads of 128 x 128 takes 30 us, in float32 26.7.
+// (7e-7, 8e-7); a chunk of 48 heads of 128 x 128 takes 29 us, in float32 26.7.
 //
-// Bound: latency, as the gated scan: a chain of phases between barriers, 30 us a
-// chunk at d = 128 with a state per 30 tokens (48 heads x 2048 tokens: 0.97 ms
-// without the readout), 29 with one per 96 (8 x 16 heads x 4k tokens).  Taking the tokens one by one, as chunks with non-finite
-// inputs, expanding steps or erased states still are, costs one barrier, a
-// reduction and a score per token, 1.5 us (48 heads x 2048 tokens 3.12 ms; 3.77
-// with two full barriers and the norms of k and v formed per token).
+// Bound: latency, as the gated scan: a chain of phases between barriers, 29 us a
+// chunk at d = 128 with a state per 30 tokens (48 heads x 2048 tokens: 0.93 ms
+// without the readout), 27 with one per 96 (8 x 16 heads x 4k tokens).  Taking the
+// tokens one by one, as chunks with non-finite inputs, expanding steps or erased
+// states still are, costs one barrier, a reduction and a score per token, 1.5 us
+// (48 heads x 2048 tokens 3.12 ms; 3.77 with two full barriers and the norms of k
+// and v formed per token).
 //
 // The call then runs the chunked update and readout stages of the gated form
 // over (q, k, u, lambda), on the gated prefill's schedule: with the scan in
