@@ -210,3 +210,15 @@ def test_token_by_token_chunks_pipelined_matches_serial(dtype, T):
                     if isinstance(a, np.ndarray)])
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_largest_capacity(dtype):
+    """1024 states of 128 x 128, the scan's largest working set in LDS, with
+    merges once the cache is full."""
+    T, C = 1100, 1024
+    w = WORKLOADS["cfg2"].replace(B=1, H=1, T=T, C=C, dtype=dtype, mean_len=2.0, seed=4)
+    x = make_inputs(w)
+    bo = np.ones((1, T), np.int8)
+    bo[:, 1050::3] = 0
+    _check(w, x, make_beta(w), bo=bo, what=f"capacity 1024 {dtype}", max_frac=0.2)
