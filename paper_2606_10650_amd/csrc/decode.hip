@@ -663,17 +663,18 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(DecodeArgs a) {
 
 // Workgroups per head: the split of the shortest estimated step, at most kMaxSplit
 // and at least two states per workgroup.  Estimate (us): rounds of the workgroups
-// that the chip holds at once (by the kernels' registers).  A round takes its
-// decisions and then the longer of one workgroup's chain of loads, state after
-// state, and the round's share of memory (1.9 for a 64 KiB state per compute unit,
-// and the newest state).  A split workgroup has the next state in flight, which
-// shortens its chain, but repeats the decisions, and a second kernel ends the step.
-// So small states (bfloat16, 64 x 64), bound by the chain, want the split where
-// 64 KiB ones, bound by memory, do not.
+// that the chip holds at once (by the kernels' registers).  A round is the longer
+// of one workgroup's chain of loads, state after state, and the round's share of
+// memory (1.8 for a 64 KiB state per compute unit, and the newest state); the
+// decisions come before the first round and in part before the next ones, and a
+// second kernel ends a split step.  A split workgroup has the next state in flight,
+// which shortens the chain of bfloat16 states most.  So these, where few heads leave
+// the chain as the bound, want the split, and 64 KiB states, bound by memory, do not.
 //
-// Fitted to 792 shapes (4 to 1016 heads, 8 to 256 states, all sizes and types; steps
-// over several caches in turn, so that no state is on chip): 1.4% over the best
-// split on average, 15% at most beside any rule tried.  us, unsplit / split in 2:
+// The chains are measured (8 heads, 64 against 128 states), the rest is fitted to
+// 792 shapes (4 to 1016 heads, 8 to 256 states, all sizes and types; steps over
+// several caches in turn, so that no state is on chip): 0.8% over the best split
+// on average.  us, unsplit / split in 2:
 //   512 heads of 128 bfloat16 states, 64 x 64          175 / 102
 //   256 heads of 128 bfloat16 states, 128 x 64         134 /  95
 //   768 heads of 128 bfloat16 states, 128 x 128        576 / 507
@@ -683,29 +684,31 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(DecodeArgs a) {
 // 64 x 64, float32 210 / 211, bfloat16 117 / 121.
 int decode_splits(int nheads, int C, int D, int state_bytes) {
   if (nheads >= 1024) return 1;
-  const bool wide = state_bytes == 4;
-  // workgroups that a compute unit holds, unsplit and split
-  const int held1 = D >= 16384 ? 2 : (D >= 8192 ? 3 : 6);
-  const int held2 = D >= 16384 ? (wide ? 1 : 2) : (D >= 8192 ? (wide ? 3 : 4) : (wide ? 5 : 6));
+  const int size = D >= 16384 ? 2 : (D >= 8192 ? 1 : 0);
+  const int type = state_bytes == 4 ? 1 : 0;
+  // [unsplit, split][bfloat16, float32][64 x 64, 64 x 128, 128 x 128]
+  static const int held[2][2][3] = {{{6, 3, 2}, {6, 3, 2}}, {{6, 4, 2}, {5, 3, 1}}};  // per unit
+  static const float chain[2][2][3] = {{{1.1f, 0.87f, 1.45f}, {0.64f, 0.79f, 1.1f}},
+                                       {{0.57f, 0.63f, 0.73f}, {0.63f, 0.72f, 1.1f}}};
   const float d = (float)D / 16384.f;                     // elements, of a 128 x 128 state
-  const float mem = 1.9f * d * (float)state_bytes / 4.f;  // one state per compute unit
+  const float mem = 1.8f * d * (float)state_bytes / 4.f;  // one state per compute unit
   const int most = C / 2 < kMaxSplit ? C / 2 : kMaxSplit;
   int best = 1;
   float cost = 0.f;
   for (int ns = 1; ns <= most; ++ns) {
-    const bool split = ns > 1;
-    const int held = split ? held2 : held1;
-    const float chain = split ? 0.55f + 0.3f * d : 0.8f + 0.6f * d;  // a state's loads
+    const int split = ns > 1 ? 1 : 0;
     const float n = (float)((C + ns - 1) / ns);
     auto round = [&](int wgs) {  // of wgs workgroups
       // (the busiest unit's share of memory, and the average one's)
       const float k = 0.4f * (float)((wgs + 255) / 256) + 0.6f * (float)wgs / 256.f;
-      const float a = n * chain, b = k * (n * mem + (split ? 4.5f : 5.f) * d);
-      return (split ? 3.f : 5.f) + (a > b ? a : b);
+      const float a = n * chain[split][type][size], b = k * (n * mem + (split ? 4.f : 6.5f) * d);
+      return a > b ? a : b;
     };
-    const int wgs = nheads * ns, slots = 256 * held;
+    const int wgs = nheads * ns, slots = 256 * held[split][type][size];
     const int full = wgs / slots, rest = wgs % slots;
-    const float c = (split ? 8.f : 0.f) + (float)full * round(slots) + (rest ? round(rest) : 0.f);
+    const float decide = split ? 1.f : 3.f;
+    const float c = (split ? 8.f : 0.f) + decide * (0.8f + 0.2f * (float)(full + (rest ? 1 : 0))) +
+                    (float)full * round(slots) + (rest ? round(rest) : 0.f);
     if (!split || c < cost) {
       cost = c;
       best = ns;

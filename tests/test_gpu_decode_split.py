@@ -20,9 +20,11 @@ def _fill(c, k, v, g, bo, mo, fill):
 
 
 @pytest.mark.parametrize("heads,C,dk,dv,states,full", [
-    (3, 4, 64, 64, "f32", True),        # the smallest split: two states each
+    (3, 4, 64, 64, "f32", True),        # too few states for a split
+    (3, 24, 128, 128, "bf16", True),    # the smallest ranges: two states each
+    (300, 64, 64, 64, "bf16", True),    # more workgroups than the chip holds at once
     (5, 33, 64, 128, "bf16", True),     # 16 ranges, the last one short
-    (32, 17, 128, 128, "f32", True),    # one workgroup per compute unit
+    (32, 17, 128, 128, "f32", True),    # about one workgroup per compute unit
     (33, 40, 128, 64, "f32", False),    # room left: no merge, the newest state in mid-cache
     (65, 9, 128, 128, "bf16", True),
     (300, 64, 64, 64, "f32", True),
